@@ -1,12 +1,13 @@
-// The other schemes of GAMER-2's fluid solver (Sec. 2.2) on padded patch
-// groups: MHM or CTU (6 Riemann solves per cell), PLM or PPM on primitive or
-// characteristic variables, generalized minmod / van Leer / van Albada /
-// hybrid limiters, HLLC / Roe / HLLE solvers.  The default scheme (MHM, PLM
-// on primitive variables, generalized minmod, HLLC) has its own fused
-// kernels (mhm_fwd.hip); this path trades their on-chip staging for a
-// general form: a chain of kernels, one thread per cell or face, passing
-// primitive states, face states and fluxes through a caller-owned workspace
-// in HBM, in the order the step defines them:
+// The scheme words of GAMER-2's fluid solver (Sec. 2.2) that need more than the
+// default march: PPM, CTU (6 Riemann solves per cell) and dual energy, on
+// padded patch groups, with any limiter, variables and solver.
+//
+// Two paths with the same arithmetic (bit-identical results): the march of
+// ext_march.h, one workgroup per z segment of a group, and, for the few
+// groups that leave it waiting on its own latency (use_chain), a chain of
+// kernels with one thread per cell or face, passing primitive states, face
+// states and fluxes through the caller's workspace in HBM in the order the
+// step defines them:
 //   1. ext_prim:    cons -> prim on the padded block                 W [5][P^3]
 //   2. ext_states:  face values and half step of every cell of
 //                   [-1, 16]^3 (MHM: Hancock with the three axes'
@@ -28,8 +29,7 @@
 // face1_idx), so that the threads of a wave, which take consecutive x,
 // touch consecutive elements whatever the axis.
 
-#include "ext_device.h"
-#include "kernels.h"
+#include "march.h"
 
 namespace gh {
 
@@ -368,7 +368,7 @@ int64_t ext_workspace_elems(int64_t n_groups, int ghost, const ExtOpts& o) {
 }
 
 template <typename T, int NF>
-hipError_t ext_step_nf(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<T>& gas, const double* dt_dev,
+hipError_t chain_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<T>& gas, const double* dt_dev,
                        double dx, const ExtOpts& o, int* n_bad, T* work, T* face_flux, hipStream_t stream) {
   const int P = 16 + 2 * ghost;
   const int64_t P3 = int64_t(P) * P * P;
@@ -399,12 +399,45 @@ hipError_t ext_step_nf(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas
   return hipGetLastError();
 }
 
+// The march's iterations are serial, each with barriers and a chain of
+// dependent arithmetic, so a step takes it at least 20-26 us (MHM), 33-38 (CTU
+// with PLM), 52-68 (CTU with PPM) however few the groups; the chain's kernels
+// run one cell or face per thread.  Measured, chain / march in us: MHM + PPM
+// FP64 4 groups 26.9 / 26.1, FP32 1 group 20.0 / 20.4, 4 groups 20.9 / 20.4;
+// with dual energy FP64 4 groups 31.7 / 32.8, 8 groups 35.1 / 33.0; CTU + PLM
+// FP64 4 groups 36.8 / 38.6, 8 groups 43.0 / 41.4, FP32 4 groups 29.0 / 33.2, 8
+// groups 34.8 / 33.7; CTU + PPM FP64 32 groups 103 / 112, 64 groups 183 / 170,
+// FP32 32 groups 61 / 63, 64 groups 97 / 82.
+bool use_chain(int64_t G, const ExtOpts& o) {
+  if (o.ctu) return G <= (o.ppm ? 40 : 6);
+  return G <= (o.de ? 5 : 2);
+}
+
+template <typename T, int NF, bool kPpm>
+hipError_t march_step(const MarchArgs<T>& A, int64_t G, hipStream_t stream) {
+  if (A.o.ctu) {
+    const hipError_t e = launch_march_mode<T, NF, kPpm, kPredict>(A, G, stream);
+    if (e != hipSuccess) return e;
+    return launch_march_mode<T, NF, kPpm, kCorrect>(A, G, stream);
+  }
+  // MHM with PLM and five fields runs in the default march
+  if constexpr (kPpm || NF == 6) return launch_march_mode<T, NF, kPpm, kStep>(A, G, stream);
+  else return hipErrorInvalidValue;
+}
+
 template <typename T>
 hipError_t launch_ext_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<T>& gas, const double* dt_dev,
                            double dx, const ExtOpts& o, int* n_bad, T* work, T* face_flux, hipStream_t stream) {
   if (G == 0) return hipSuccess;
-  if (o.de) return ext_step_nf<T, 6>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, nullptr, stream);
-  return ext_step_nf<T, 5>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, face_flux, stream);
+  if (use_chain(G, o)) {
+    if (o.de) return chain_step<T, 6>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, nullptr, stream);
+    return chain_step<T, 5>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, face_flux, stream);
+  }
+  // CTU's flux differences take the first 3 NF blocks of 18^3 per group of the
+  // workspace (it holds 6 NF blocks of face states for every group)
+  const MarchArgs<T> A{U_pad, U_out, ghost, 1, gas, dt_dev, dx, o, T(o.xi), n_bad, o.de ? nullptr : face_flux, work};
+  if (o.de) return o.ppm ? march_step<T, 6, true>(A, G, stream) : march_step<T, 6, false>(A, G, stream);
+  return o.ppm ? march_step<T, 5, true>(A, G, stream) : march_step<T, 5, false>(A, G, stream);
 }
 
 template hipError_t launch_ext_step<double>(const double*, double*, int64_t, int, const Gas<double>&, const double*,
