@@ -49,7 +49,9 @@ struct hydro_ctx {
   std::string cache_path;
   bool require_tuned = false;
   int level_sel[2][2] = {{-1, -1}, {-1, -1}};  // [dtype][with CFL epilogue], -1 = not set
+  bool level_explicit[2][2] = {{false, false}, {false, false}};  // set by the caller, not by the tuner
   int batched_sel[2] = {-1, -1};
+  bool batched_explicit[2] = {false, false};
   int adjoint_sel[2] = {-1, -1};
   std::map<std::string, int> tuned;          // autotuned or cached selections by key
   std::set<void*> graphs;                    // hipGraphExec_t handles captured through this context
@@ -106,6 +108,21 @@ int select_shape(hydro_ctx* c, const std::string& key, const int* explicit_sel, 
   if (c->require_tuned) return HYDRO_ENOTUNED;
   *out = fallback;
   return HYDRO_OK;
+}
+
+// Whether the caller set the level step's shape itself (hydro_set_variant):
+// then exactly that shape runs.  A tuned or default shape stands for whole
+// groups, and a level of few groups may split them (plm_segments).
+bool shape_is_explicit(hydro_ctx* c, int32_t dtype, bool with_cfl) {
+  if (c == nullptr) return false;
+  std::lock_guard<std::mutex> lk(c->mu);
+  return c->level_explicit[dtype][with_cfl ? 1 : 0];
+}
+
+bool batched_is_explicit(hydro_ctx* c, int32_t dtype) {
+  if (c == nullptr) return false;
+  std::lock_guard<std::mutex> lk(c->mu);
+  return c->batched_explicit[dtype];
 }
 
 // Tuning cache: a JSON object {"version": 1, "entries": {"<key>": <shape>, ...}}.
@@ -248,8 +265,9 @@ gh::Gas<T> make_gas(double gamma, double theta, double dt, double dx) {
 
 template <typename T>
 int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_t scheme, double theta,
-                 int32_t* n_bad_dev, uint32_t* work_dev, int32_t grid, int variant, hipStream_t s) {
+                 int32_t* n_bad_dev, uint32_t* work_dev, int32_t grid, int variant, bool split, hipStream_t s) {
   gh::BatchArgs<T> a;
+  bool patches = false;
   a.n_levels = n_levels;
   a.cfl = 0;
   long long total = 0;
@@ -274,6 +292,7 @@ int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_
     b.c_cfl_dx = lv[l].c_cfl * lv[l].dx;
     b.fold_scale = lv[l].dt_next_scale == 0.0 ? 1.0 : lv[l].dt_next_scale;
     a.cfl = a.cfl || b.dt_patch != nullptr || b.dt_min != nullptr || b.reset != nullptr;
+    patches = patches || b.dt_patch != nullptr;
     total += (long long)lv[l].ngx * lv[l].ngy * lv[l].ngz;
   }
   for (int l = n_levels; l < gh::kMaxLevels; ++l) {
@@ -288,6 +307,10 @@ int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_
   if (g > total) g = total;
   gh::Gas<T> gas = make_gas<T>(gamma, theta, 1.0, 1.0);
   const int fo = (scheme & HYDRO_FIRST_ORDER) ? 1 : 0, ws = (scheme >> 8) & 3;
+  // few groups: shared by several workgroups each, without a queue (unless the
+  // caller chose the shape or the grid itself)
+  const int segs = split && grid == 0 ? gh::plm_segments<T>(total, patches) : 1;
+  if (segs > 1) return device_status(gh::launch_mhm_batched_seg<T>(a, gas, fo, ws, n_bad_dev, segs, s));
   // work_dev NULL: the allocation-free entry point (the library's own counters)
   if (work_dev == nullptr)
     return device_status(gh::launch_mhm_batched_noalloc<T>(a, gas, fo, ws, n_bad_dev, variant, int(g), s));
@@ -381,7 +404,7 @@ int check_level_args(const void* level_dev, const void* level_out_dev, int32_t n
 int level_launch(const void* level_dev, void* level_out_dev, const gh::LevelGeom& geo, int32_t dtype, double dt,
                  double dx, double gamma, int32_t scheme, double theta, const double* dt_dev, int32_t* n_bad_dev,
                  double c_cfl, double* dt_next_dev, double* dt_patch_next_dev, double* dt_reset_dev, int variant,
-                 hipStream_t s) {
+                 bool split, hipStream_t s) {
   gh::CflOut cfl;
   cfl.dt_patch = dt_patch_next_dev;
   cfl.dt_min = reinterpret_cast<unsigned long long*>(dt_next_dev);
@@ -396,11 +419,11 @@ int level_launch(const void* level_dev, void* level_out_dev, const gh::LevelGeom
   if (dtype == HYDRO_F64)
     e = gh::launch_mhm_level(static_cast<const double*>(level_dev), static_cast<double*>(level_out_dev), geo,
                              make_gas<double>(gamma, theta, dt_host, dx), dt_dev, dx, first_order, ws, n_bad_dev, cfl,
-                             variant, s);
+                             variant, split, s);
   else
     e = gh::launch_mhm_level(static_cast<const float*>(level_dev), static_cast<float*>(level_out_dev), geo,
                              make_gas<float>(gamma, theta, dt_host, dx), dt_dev, dx, first_order, ws, n_bad_dev, cfl,
-                             variant, s);
+                             variant, split, s);
   return device_status(e);
 }
 
@@ -454,10 +477,12 @@ int level_adjoint_launch(const void* level_dev, const void* g_level_out_dev, voi
 }
 
 int batched_launch(const hydro_level_t* levels_host, int32_t n_levels, int32_t dtype, double gamma, int32_t scheme,
-                   double theta, int32_t* n_bad_dev, uint32_t* work_dev, int32_t grid, int variant, hipStream_t s) {
+                   double theta, int32_t* n_bad_dev, uint32_t* work_dev, int32_t grid, int variant, bool split,
+                   hipStream_t s) {
   if (dtype == HYDRO_F64)
-    return batched_impl<double>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, s);
-  return batched_impl<float>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, s);
+    return batched_impl<double>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, split,
+                                s);
+  return batched_impl<float>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, split, s);
 }
 
 // Preference among launch shapes that time as ties: XCD-blocked before
@@ -964,7 +989,7 @@ int hydro_advance_level_fallback(hydro_ctx* ctx, const void* level_in_dev, void*
     if (e != hipSuccess) return device_status(e);
     if (fused) {
       st = level_launch(level_in_dev, level_out_dev, geo, dtype, dt, dx, gamma, scheme, theta, nullptr, cnt + 3, 0.0,
-                        nullptr, nullptr, nullptr, variant, s);
+                        nullptr, nullptr, nullptr, variant, !shape_is_explicit(ctx, dtype, false), s);
     } else {
       e = dtype == HYDRO_F64
               ? gh::launch_fill_ghosts(static_cast<const double*>(level_in_dev), reinterpret_cast<double*>(pad), ngx,
@@ -1016,7 +1041,8 @@ int hydro_advance_level(hydro_ctx* ctx, const void* level_dev, void* level_out_d
                     ctx ? &ctx->level_sel[dtype][with_cfl ? 1 : 0] : nullptr, kDefaultLevelVariant, &variant);
   if (st != HYDRO_OK) return st;
   return level_launch(level_dev, level_out_dev, geo, dtype, dt, dx, gamma, scheme, theta, dt_dev, n_bad_dev, c_cfl,
-                      dt_next_dev, dt_patch_next_dev, dt_reset_dev, variant, static_cast<hipStream_t>(stream));
+                      dt_next_dev, dt_patch_next_dev, dt_reset_dev, variant,
+                      !shape_is_explicit(ctx, dtype, with_cfl), static_cast<hipStream_t>(stream));
 }
 
 int hydro_num_variants(void) { return gh::kLevelVariants; }
@@ -1034,6 +1060,7 @@ int hydro_set_level_variant(hydro_ctx* ctx, int32_t dtype, int32_t with_cfl, int
   if (variant < 0 || variant >= gh::kLevelVariants) return HYDRO_EINVAL;
   std::lock_guard<std::mutex> lk(ctx->mu);
   ctx->level_sel[dtype][with_cfl ? 1 : 0] = variant;
+  ctx->level_explicit[dtype][with_cfl ? 1 : 0] = true;
   // an explicit choice overrides earlier tuned choices of this dtype and form
   const std::string prefix = std::string("level/") + dtype_name(dtype) + (with_cfl ? "/cfl/" : "/plain/");
   for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
@@ -1084,7 +1111,7 @@ int hydro_autotune(hydro_ctx* ctx, const void* level_dev, void* scratch_out_dev,
     double* dt_patch = form ? cfl_scratch_dev + 3 : nullptr;
     best[form] = time_shapes(gh::kLevelVariants, reps, s, ms[form], [&](int v) {
       return level_launch(level_dev, scratch_out_dev, geo, dtype, dt, dx, gamma, HYDRO_SCHEME_MHM_PLM_HLLC, 1.5,
-                          nullptr, nullptr, 0.5, dt_next, dt_patch, dt_reset, v, s);
+                          nullptr, nullptr, 0.5, dt_next, dt_patch, dt_reset, v, false, s);
     });
     if (best[form] < 0) return best[form];
     // The tuner relaunches one input, which stays partly in the caches; a
@@ -1109,6 +1136,7 @@ int hydro_autotune(hydro_ctx* ctx, const void* level_dev, void* scratch_out_dev,
     ctx->tuned[level_key(dtype, true, ngx, ngy, ngz)] = best[1];
     ctx->level_sel[dtype][0] = best[0];
     ctx->level_sel[dtype][1] = best[1];
+    ctx->level_explicit[dtype][0] = ctx->level_explicit[dtype][1] = false;
     (void)save_cache_locked(ctx);
   }
   return best[1];
@@ -1128,7 +1156,7 @@ int hydro_advance_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int3
                     kDefaultBatchedVariant, &variant);
   if (st != HYDRO_OK) return st;
   return batched_launch(levels_host, n_levels, dtype, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant,
-                        static_cast<hipStream_t>(stream));
+                        !batched_is_explicit(ctx, dtype), static_cast<hipStream_t>(stream));
 }
 
 int hydro_advance_batched_noalloc(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels,
@@ -1144,7 +1172,7 @@ int hydro_advance_batched_noalloc(hydro_ctx* ctx, const hydro_level_t* levels_ho
                     kDefaultBatchedVariant, &variant);
   if (st != HYDRO_OK) return st;
   return batched_launch(levels_host, n_levels, dtype, gamma, scheme, theta, n_bad_dev, nullptr, grid, variant,
-                        static_cast<hipStream_t>(stream));
+                        !batched_is_explicit(ctx, dtype), static_cast<hipStream_t>(stream));
 }
 
 int hydro_set_batched_variant(hydro_ctx* ctx, int32_t dtype, int32_t variant) {
@@ -1152,6 +1180,7 @@ int hydro_set_batched_variant(hydro_ctx* ctx, int32_t dtype, int32_t variant) {
   if (variant < 0 || variant >= gh::kBatchedVariants) return HYDRO_EINVAL;
   std::lock_guard<std::mutex> lk(ctx->mu);
   ctx->batched_sel[dtype] = variant;
+  ctx->batched_explicit[dtype] = true;
   const std::string prefix = std::string("batched/") + dtype_name(dtype) + "/";
   for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
     it = it->first.compare(0, prefix.size(), prefix) == 0 ? ctx->tuned.erase(it) : std::next(it);
@@ -1176,7 +1205,7 @@ int hydro_autotune_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int
   float ms[gh::kBatchedVariants] = {};
   const int best = time_shapes(gh::kBatchedVariants, reps, s, ms, [&](int var) {
     return batched_launch(levels_host, n_levels, dtype, gamma, HYDRO_SCHEME_MHM_PLM_HLLC, 1.5, nullptr, work_dev, 0,
-                          var, s);
+                          var, false, s);
   });
   if (best < 0) return best;
   if (times_ms_host != nullptr)

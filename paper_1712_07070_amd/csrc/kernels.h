@@ -41,7 +41,8 @@ inline int march_segments(int64_t G, int slots, double share) {
     const int64_t n = (G * s + 255) / 256, rest = n % slots;
     const double full = double(n / slots) * (1.0 + share * (slots - 1));
     const double c = (full + (rest ? 1.0 + share * double(rest - 1) : 0.0)) * (16 / s + 2);
-    if (s == 1 || c < cost) {
+    if (s == 1) cost = 0.9 * c;  // a split has to gain clearly
+    else if (c < cost) {
       best = s;
       cost = c;
     }
@@ -49,10 +50,46 @@ inline int march_segments(int64_t G, int slots, double share) {
   return best;
 }
 
+// Segments per group of the default march and of the other PLM words' (FP64
+// two workgroups to a compute unit, FP32 three).  whole_halves: per-patch
+// time-steps are written, so no segment may hold part of a patch.  Padded
+// step by 1, 2, 4, 8, 16 segments, us: FP64 8 groups 73, 46, 27, 17, 12; 64
+// groups 74, 47, 28, 27, 36; 192 groups 75, 66, 62, 68, 86; 512 groups 113, 129,
+// 142, 169, 213.  FP32 64 groups 59, 38, 23, 17, 22; 336 groups 71, 53, 57, 62,
+// 78; 512 groups 72, 79, 76, 87, 115.
+template <typename T>
+int plm_segments(int64_t G, bool whole_halves) {
+  const int s = sizeof(T) == 8 ? march_segments(G, 2, 0.5) : march_segments(G, 3, 0.22);
+  return whole_halves && s > 2 ? 2 : s;
+}
+
+// split: groups may be shared by several workgroups (plm_segments); else
+// exactly the shape `variant`.
 template <typename T>
 hipError_t launch_mhm_level(const T* level, T* level_out, const LevelGeom& geo, const Gas<T>& gas,
                             const double* dt_dev, double dx, int first_order, int ws, int* n_bad, const CflOut& cfl,
-                            int variant, hipStream_t stream);
+                            int variant, bool split, hipStream_t stream);
+
+// The steps with every group shared by `segs` workgroups, one per z segment
+// (mhm_seg.hip; levels of fewer than 2^32 elements).
+template <typename T>
+hipError_t launch_mhm_level_seg(const T* level, T* level_out, const LevelGeom& geo, const Gas<T>& gas,
+                                const double* dt_dev, double dx, int first_order, int ws, int* n_bad,
+                                const CflOut& cfl, int segs, hipStream_t stream);
+template <typename T>
+hipError_t launch_mhm_fwd_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
+                              const double* dt_dev, double dx, int first_order, int ws, int* n_bad,
+                              hipStream_t stream, T* face_flux, int segs);
+template <typename T>
+struct BatchArgs;
+template <typename T>
+hipError_t launch_mhm_batched_seg(const BatchArgs<T>& args, const Gas<T>& gas, int first_order, int ws, int* n_bad,
+                                  int segs, hipStream_t stream);
+struct ExtOpts;
+template <typename T>
+hipError_t launch_mhm_fwd_ext_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
+                                  const double* dt_dev, double dx, const ExtOpts& o, int* n_bad, hipStream_t stream,
+                                  T* face_flux, int segs);
 
 // One level of a batched launch: input / output level storage, geometry,
 // the level's dt/dx (or a device dt), and the index of its first work item.

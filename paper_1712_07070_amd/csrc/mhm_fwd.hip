@@ -114,6 +114,10 @@ hipError_t launch_mhm_fwd(const T* U_pad, T* U_out, int64_t n_groups, int ghost,
                           const double* dt_dev, double dx, int first_order, int ws, int* n_bad,
                           hipStream_t stream, T* face_flux) {
   if (n_groups == 0) return hipSuccess;
+  const int segs = plm_segments<T>(n_groups, false);
+  if (segs > 1)
+    return launch_mhm_fwd_seg(U_pad, U_out, int(n_groups), ghost, gas, dt_dev, dx, first_order, ws, n_bad, stream,
+                              face_flux, segs);
   // one workgroup per group; very large batches go in launches of at most
   // 2^30 workgroups
   const int64_t chunk = int64_t(1) << 30;
@@ -142,10 +146,13 @@ hipError_t launch_mhm_fwd(const T* U_pad, T* U_out, int64_t n_groups, int ghost,
 template <typename T>
 hipError_t launch_mhm_level(const T* level, T* level_out, const LevelGeom& geo, const Gas<T>& gas,
                             const double* dt_dev, double dx, int first_order, int ws, int* n_bad, const CflOut& cfl,
-                            int variant, hipStream_t stream) {
+                            int variant, bool split, hipStream_t stream) {
   const int64_t G = int64_t(geo.ngx) * geo.ngy * geo.ngz;
   if (G == 0) return hipSuccess;
   if (G > (int64_t(1) << 31) - 8) return hipErrorInvalidValue;
+  const int segs = split ? plm_segments<T>(G, cfl.dt_patch != nullptr) : 1;
+  if (segs > 1)
+    return launch_mhm_level_seg(level, level_out, geo, gas, dt_dev, dx, first_order, ws, n_bad, cfl, segs, stream);
   const bool with_cfl = cfl.dt_min != nullptr || cfl.dt_patch != nullptr || cfl.reset != nullptr;
   if (with_cfl)
     return launch_level_variant<T, true>(level, level_out, geo, gas, dt_dev, dx, first_order, ws, n_bad, cfl, variant,
@@ -171,8 +178,10 @@ template hipError_t launch_mhm_fwd<double>(const double*, double*, int64_t, int,
 template hipError_t launch_mhm_fwd<float>(const float*, float*, int64_t, int, const Gas<float>&,
                                           const double*, double, int, int, int*, hipStream_t, float*);
 template hipError_t launch_mhm_level<double>(const double*, double*, const LevelGeom&, const Gas<double>&,
-                                             const double*, double, int, int, int*, const CflOut&, int, hipStream_t);
+                                             const double*, double, int, int, int*, const CflOut&, int, bool,
+                                             hipStream_t);
 template hipError_t launch_mhm_level<float>(const float*, float*, const LevelGeom&, const Gas<float>&,
-                                            const double*, double, int, int, int*, const CflOut&, int, hipStream_t);
+                                            const double*, double, int, int, int*, const CflOut&, int, bool,
+                                            hipStream_t);
 
 }  // namespace gh

@@ -59,6 +59,10 @@ hipError_t launch_mhm_fwd_ext(const T* U_pad, T* U_out, int64_t n_groups, int gh
                               const double* dt_dev, double dx, const ExtOpts& o, int* n_bad, hipStream_t stream,
                               T* face_flux) {
   if (n_groups == 0) return hipSuccess;
+  const int segs = plm_segments<T>(n_groups, false);
+  if (segs > 1)
+    return launch_mhm_fwd_ext_seg(U_pad, U_out, int(n_groups), ghost, gas, dt_dev, dx, o, n_bad, stream, face_flux,
+                                  segs);
   const int64_t chunk = int64_t(1) << 30;
   const int P = 16 + 2 * ghost;
   const int64_t P3 = int64_t(P) * P * P;

@@ -221,10 +221,20 @@ __device__ __forceinline__ int scheme_flux2(const ExtSchemeT<kChr, kRoe>& sch, c
 // faces on the high x and y boundary of the group (their high-side states
 // come from the halo role through LDS) after its own faces.
 
+// The planes [lo, hi) of the group a workgroup completes: all of them, or one
+// z segment (the march then runs the planes lo - 1 .. hi, recomputing the
+// states of one plane beyond each end; the face between two segments is
+// solved by both and counted by the upper one).
+struct ZAll {
+  static constexpr int lo = 0, hi = 16;
+};
+struct ZPart {
+  int lo, hi;
+};
+
 // Per-column state of one role across the z-march.
 template <typename T, bool kInterior, typename Off>
 struct FwdCol {
-  static constexpr int zhi = kInterior ? 17 : 16;  // last plane of the column that is read
   int cx, cy;
   bool xface16, yface16;  // halo columns at x = 16 / y = 16 (high side of the last x / y face)
   Off col;
@@ -234,22 +244,23 @@ struct FwdCol {
   T Uz[5], Fz0[5];        // interior: z+ face state of plane k-1; z flux at the low face of plane k-1
 };
 
-template <typename T, bool kI, class Src>
-__device__ __forceinline__ void fwd_col_init(FwdCol<T, kI, typename Src::Off>& c, const Src& src, int cx, int cy, const Gas<T>& gas) {
+template <typename T, bool kI, class Src, class Z>
+__device__ __forceinline__ void fwd_col_init(FwdCol<T, kI, typename Src::Off>& c, const Src& src, int cx, int cy, const Gas<T>& gas, const Z& zr) {
   c.cx = cx;
   c.cy = cy;
   c.xface16 = !kI && cx == 16;
   c.yface16 = !kI && cy == 16;
   c.col = src.col(cx, cy);
-  if (kI) load_prim(src, c.col, -2, gas, c.Wm);
-  load_prim(src, c.col, -1, gas, c.Wc);
-  load_cons(src, c.col, 0, c.Un);
+  if (kI) load_prim(src, c.col, zr.lo - 2, gas, c.Wm);
+  load_prim(src, c.col, zr.lo - 1, gas, c.Wc);
+  load_cons(src, c.col, zr.lo, c.Un);
 }
 
 // Next plane of the column (prefetched one iteration ahead); publish plane k.
-template <typename T, bool kI, class Src, int kL>
+template <typename T, bool kI, class Src, int kL, class Z>
 __device__ __forceinline__ void fwd_col_publish(FwdCol<T, kI, typename Src::Off>& c, const Src& src, int k, const Gas<T>& gas,
-                                                Smem<T, kL>& sm) {
+                                                Smem<T, kL>& sm, const Z& zr) {
+  const int zhi = kI ? zr.hi + 1 : zr.hi;  // last plane of the column that is read
   // Convert the plane that arrived, then issue the next one.  The load is
   // unconditional (plane index clamped to the column's last plane, re-read
   // harmlessly near the top) and issued after the conversion, so the loaded
@@ -257,7 +268,7 @@ __device__ __forceinline__ void fwd_col_publish(FwdCol<T, kI, typename Src::Off>
   // and wait for the load that is meant to stay in flight.
   cons_to_prim(c.Un, gas, c.Wp);
   asm volatile("" ::: "memory");
-  load_cons(src, c.col, k + 2 <= c.zhi ? k + 2 : c.zhi, c.Un);
+  load_cons(src, c.col, k + 2 <= zhi ? k + 2 : zhi, c.Un);
 #pragma unroll
   for (int q = 0; q < 5; ++q) sm.P[q][sm.pi(c.cx, c.cy)] = c.Wc[q];
 }
@@ -275,26 +286,26 @@ __device__ __forceinline__ int cfl_slot(int tid) {
 
 // Half-step face states of the column's state cell at plane k.  Interior
 // columns also solve the z-face k-1/2 and complete plane k-1.
-template <typename T, bool kI, class Src, int kL, class Sch>
+template <typename T, bool kI, class Src, int kL, class Sch, class Z>
 __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, typename Src::Off>& c, const Src& src, T* __restrict__ out, int k,
                                               const Gas<T>& gas, int first_order, int ws, Smem<T, kL>& sm, double* smax,
-                                              double gamma_d, T* __restrict__ ff, unsigned* rec) {
+                                              double gamma_d, T* __restrict__ ff, unsigned* rec, const Z& zr) {
   const int cx = c.cx, cy = c.cy;
   int bad = 0;
   // U^n of plane k-1 for its update at the end of this phase, issued first
   // so that the load's latency overlaps the half step and the z-face solve
   T Uold[5];
-  if (kI && k >= 1) load_cons(src, c.col, k - 1, Uold);
+  if (kI && k > zr.lo) load_cons(src, c.col, k - 1, Uold);
   // x/y flux differences of plane k-1 (fluxes written last iteration)
   T acc[5];
-  if (kI && k >= 1) {
+  if (kI && k > zr.lo) {
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       acc[q] = sm.F[0][q][fxidx(cx + 1, cy)] - sm.F[0][q][fxidx(cx, cy)];
       acc[q] = acc[q] + (sm.F[1][q][fyidx(cx, cy + 1)] - sm.F[1][q][fyidx(cx, cy)]);
     }
   }
-  if (!kI && (k < 0 || k > 15)) return 0;
+  if (!kI && (k < zr.lo || k >= zr.hi)) return 0;
   T Wn[3][2][5];
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
@@ -324,16 +335,19 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
     for (int q = 0; q < 5; ++q) sm.H[q][slot] = c.xface16 ? Ut[0][0][q] : Ut[1][0][q];
   }
   if (kI) {
-    if (k >= 0) {
+    if (k >= zr.lo) {
       T Fz1[5];
-      bad += scheme_flux<2>(sch, c.Uz, Ut[2][0], gas, ws, Fz1, rec);
-      if (ff != nullptr && (k & 7) == 0) {
+      const int bz = scheme_flux<2>(sch, c.Uz, Ut[2][0], gas, ws, Fz1, rec);
+      bool own = true;
+      if constexpr (!std::is_same<Z, ZAll>::value) own = k < zr.hi || zr.hi == 16;
+      bad += own ? bz : 0;
+      if (ff != nullptr && (k & 7) == 0 && own) {
         // z faces on a patch boundary (z = 0, 8, 16): plane 6 + k/8, entry y*16 + x
         T* o = ff + (6 + (k >> 3)) * 5 * 256 + cy * 16 + cx;
 #pragma unroll
         for (int q = 0; q < 5; ++q) o[q * 256] = Fz1[q];
       }
-      if (k >= 1) {
+      if (k > zr.lo) {
         // complete plane k-1: U^{n+1} = U^n - dt/dx [(x) + (y) + (z)]
         T Un[5];
 #pragma unroll
@@ -361,10 +375,10 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
 
 // x and y faces of plane k that an interior column solves: its low x and low
 // y face.
-template <typename T, bool kI, typename Off, int kL, class Sch>
+template <typename T, bool kI, typename Off, int kL, class Sch, class Z>
 __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>& c, int k, const Gas<T>& gas, int ws, Smem<T, kL>& sm,
-                                             T* __restrict__ ff, unsigned* rec) {
-  if (!kI || k < 0 || k > 15) return 0;
+                                             T* __restrict__ ff, unsigned* rec, const Z& zr) {
+  if (!kI || k < zr.lo || k >= zr.hi) return 0;
   const int cx = c.cx, cy = c.cy;
   T Lx[5], Fx[5], Ly[5], Fy[5];
 #pragma unroll
@@ -399,10 +413,10 @@ __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>&
 // m_y, m_z), the same arithmetic on the same values as the y-normal solver,
 // and the flux rotated back.  The halo wave wrote the high-side states to
 // H; this pass runs on another wave, which has no halo work.
-template <typename T, int kL, class Sch>
+template <typename T, int kL, class Sch, class Z>
 __device__ __forceinline__ int last_faces(const Sch& sch, int lane, int k, const Gas<T>& gas, int ws, Smem<T, kL>& sm,
-                                          T* __restrict__ ff, unsigned* rec) {
-  if (k < 0 || k > 15 || lane >= 32) return 0;
+                                          T* __restrict__ ff, unsigned* rec, const Z& zr) {
+  if (k < zr.lo || k >= zr.hi || lane >= 32) return 0;
   const bool yf = lane >= 16;
   const int i = lane & 15;
   const T* Sb = yf ? &sm.S[1][0][sm.si(i, 15)] : &sm.S[0][0][sm.si(15, i)];
@@ -456,10 +470,10 @@ enum WaveRole { kRoleHalo = 0, kRoleLastFaces = 1, kRolePlain = 2 };
 // The z-march of one wave: interior role, plus the halo roles (kRoleHalo,
 // wave 0) or the solve of the 32 last faces (kRoleLastFaces, wave 2).  Every
 // instantiation passes the same barriers in the same order.
-template <typename T, class Src, int kRole, int kUnroll, int kL, class Sch>
+template <typename T, class Src, int kRole, int kUnroll, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas, int first_order,
                                            int ws, Smem<T, kL>& sm, double* smax, double gamma_d, int tid,
-                                           T* __restrict__ ff, unsigned* rec) {
+                                           T* __restrict__ ff, unsigned* rec, const Z& zr) {
   // halo role: side 0..3 = x-, x+, y-, y+; the column two cells out; lanes
   // 0..3 also one of the 4 edge columns
   const int lane = tid & 63;
@@ -473,34 +487,34 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
   using Off = typename Src::Off;
   FwdCol<T, true, Off> ci;
   FwdCol<T, false, Off> ch;
-  fwd_col_init(ci, src, tid & 15, tid >> 4, gas);
+  fwd_col_init(ci, src, tid & 15, tid >> 4, gas, zr);
   Off col_out = 0, col_edge = 0;
   T Uo[5], Ue[5];  // halo role: 2-deep and edge column, plane k (in flight)
   if (kHalo) {
     col_out = src.col(ox, oy);
     col_edge = src.col(has_edge ? ex : ox, has_edge ? ey : oy);  // lanes without an edge re-read their 2-deep column
-    fwd_col_init(ch, src, hx, hy, gas);
-    load_cons(src, col_out, 0, Uo);
-    load_cons(src, col_edge, 0, Ue);
+    fwd_col_init(ch, src, hx, hy, gas, zr);
+    load_cons(src, col_out, zr.lo, Uo);
+    load_cons(src, col_edge, zr.lo, Ue);
   }
   int bad = 0;
 
 #pragma unroll kUnroll
-  for (int k = -1; k <= 16; ++k) {
+  for (int k = zr.lo - 1; k <= zr.hi; ++k) {
     // ---- next planes (prefetched); publish plane k to LDS
-    fwd_col_publish(ci, src, k, gas, sm);
+    fwd_col_publish(ci, src, k, gas, sm, zr);
     if (kHalo) {
-      fwd_col_publish(ch, src, k, gas, sm);
-      // 2-deep and edge columns (planes 0..15; loads clamped, no merge of
+      fwd_col_publish(ch, src, k, gas, sm, zr);
+      // 2-deep and edge columns (planes lo..hi-1; loads clamped, no merge of
       // loaded registers with old values)
       T Wo[5], We[5];
       cons_to_prim(Uo, gas, Wo);
       cons_to_prim(Ue, gas, We);
       asm volatile("" ::: "memory");
-      const int kn = k + 1 < 0 ? 0 : (k + 1 > 15 ? 15 : k + 1);
+      const int kn = k + 1 < zr.lo ? zr.lo : (k + 1 >= zr.hi ? zr.hi - 1 : k + 1);
       load_cons(src, col_out, kn, Uo);
       load_cons(src, col_edge, kn, Ue);
-      if (k >= 0 && k <= 15) {
+      if (k >= zr.lo && k < zr.hi) {
 #pragma unroll
         for (int q = 0; q < 5; ++q) sm.P[q][sm.pi(ox, oy)] = Wo[q];
         if (has_edge) {
@@ -512,13 +526,13 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
     __syncthreads();
 
     // ---- half-step face states of plane k; z-face and update of plane k-1
-    bad += fwd_col_states(sch, ci, src, out, k, gas, first_order, ws, sm, smax, gamma_d, ff, rec);
-    if (kHalo) bad += fwd_col_states(sch, ch, src, out, k, gas, first_order, ws, sm, nullptr, gamma_d, (T*)nullptr, rec);
+    bad += fwd_col_states(sch, ci, src, out, k, gas, first_order, ws, sm, smax, gamma_d, ff, rec, zr);
+    if (kHalo) bad += fwd_col_states(sch, ch, src, out, k, gas, first_order, ws, sm, nullptr, gamma_d, (T*)nullptr, rec, zr);
     __syncthreads();
 
     // ---- x and y faces of plane k
-    bad += fwd_col_faces(sch, ci, k, gas, ws, sm, ff, rec);
-    if (kRole == kRoleLastFaces) bad += last_faces(sch, lane, k, gas, ws, sm, ff, rec);
+    bad += fwd_col_faces(sch, ci, k, gas, ws, sm, ff, rec, zr);
+    if (kRole == kRoleLastFaces) bad += last_faces(sch, lane, k, gas, ws, sm, ff, rec, zr);
 
     fwd_col_shift(ci);
     if (kHalo) fwd_col_shift(ch);
@@ -549,10 +563,10 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 // waves per SIMD (FP32, high occupancy) the step is 6-8% faster; with two
 // (FP64, FP32 low occupancy) 2-5% slower, so those kernels keep equal
 // priorities.
-template <typename T, bool kPrio, class Src, int kL, class Sch>
+template <typename T, bool kPrio, class Src, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas,
                                            int first_order, int ws, Smem<T, kL>& sm, double* smax, double gamma_d,
-                                           int tid, T* __restrict__ ff, unsigned* rec) {
+                                           int tid, T* __restrict__ ff, unsigned* rec, const Z& zr) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Two planes per loop iteration, so that the register rotation of a
   // column's planes (Wm <- Wc <- Wp, z-face state and flux) becomes renaming
@@ -568,42 +582,49 @@ __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __
     if (wave == 0) __builtin_amdgcn_s_setprio(2);
     if (wave == 2) __builtin_amdgcn_s_setprio(1);
   }
-  if constexpr (!std::is_same<Sch, DefaultScheme>::value) {
+  if constexpr (std::is_same<Z, ZPart>::value) {
+    // a z segment: few planes, one per loop iteration, one copy
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    if (wave == 2)
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+  } else if constexpr (!std::is_same<Sch, DefaultScheme>::value) {
     // the other words: one copy (their options are run-time anyway), one
     // plane per loop iteration
-    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
-    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
   } else {
     if (first_order == 0) {
-      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec);
+      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
       if (wave == 2)
-        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec);
-      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec);
+        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
     }
     if (wave == 0)
-      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
+      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
-    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec);
+      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
   }
 }
 
 // rec_out (diagnostic, optional): the group's branch record -- every
 // thread's decisions hashed in its own order (record()), the threads' hashes
 // combined by XOR, which is independent of the order they arrive in.
-template <typename T, bool kPrio, class Src, int kL, class Sch = DefaultScheme>
+template <typename T, bool kPrio, class Src, int kL, class Sch = DefaultScheme, class Z = ZAll>
 __device__ __forceinline__ int process_group(const Src& src, T* __restrict__ out, const Gas<T>& gas,
                                              int first_order, int ws, Smem<T, kL>& sm, double* smax,
                                              double gamma_d, int tid = threadIdx.x, T* __restrict__ ff = nullptr,
-                                             unsigned* __restrict__ rec_out = nullptr, const Sch& sch = Sch()) {
+                                             unsigned* __restrict__ rec_out = nullptr, const Sch& sch = Sch(),
+                                             const Z& zr = Z()) {
   if (rec_out == nullptr)
-    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr);
+    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr, zr);
   __shared__ unsigned grp_rec;
   if (tid == 0) grp_rec = 0u;  // the march's first barrier orders this before any XOR
   unsigned h = 2166136261u ^ (unsigned(tid) * 0x9E3779B9u);
-  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h);
+  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h, zr);
   atomicXor(&grp_rec, h);
   __syncthreads();
   if (tid == 0) *rec_out = grp_rec;
@@ -618,13 +639,14 @@ __device__ __forceinline__ int process_group(const Src& src, T* __restrict__ out
 // 4 waves (each wave two patches) was measured slower on the 256^3 step (FP64
 // 0.904 vs 0.881 ms, FP32 0.553 vs 0.493 ms).  Stores dt_patch[p]
 // (optional) and folds dt * fold_scale into *dt_min (optional; integer
-// minimum of non-negative doubles: exact and order-independent).  Every
-// thread of the workgroup must call it.
+// minimum of non-negative doubles: exact and order-independent).  half >= 0:
+// only the patches of that z half (a workgroup that completed part of the
+// group).  Every thread of the workgroup must call it.
 __device__ __forceinline__ void cfl_epilogue(const double* slots, double c_cfl_dx,
                                              double* __restrict__ dt_patch, unsigned long long* __restrict__ dt_min,
-                                             double fold_scale = 1.0, int tid = threadIdx.x) {
+                                             double fold_scale = 1.0, int tid = threadIdx.x, int half = -1) {
   __syncthreads();
-  if (tid < 8) {
+  if (tid < 8 && (half < 0 || tid >> 2 == half)) {
     double m = 0.0;
     for (int i = 0; i < 64; ++i) {
       const double s = slots[tid * 64 + i];

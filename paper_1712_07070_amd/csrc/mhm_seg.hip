@@ -1,0 +1,197 @@
+// The MHM step of few groups: every group's planes shared by several
+// workgroups, each marching one z segment (ZPart, mhm_group.h).  One
+// workgroup per group leaves the chip idle below 256 groups (one per compute
+// unit), and a march of 18 iterations takes about 75 us (FP64) however few
+// the groups; a segment of n planes runs n + 2.  Same arithmetic, same bits.
+// Sources and outputs as in mhm_fwd.hip and mhm_fwd_ext.hip.
+
+#include "mhm_group.h"
+
+namespace gh {
+
+namespace {
+
+// The low occupancy target in FP32 and the high one in FP64: two waves per
+// SIMD in both, as for the whole-group kernels.
+template <typename T>
+constexpr int kSegWaves = 2;
+
+template <typename T, bool kCfl>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_level_seg_kernel(
+    const T* __restrict__ level, T* __restrict__ level_out, LevelGeom geo, Gas<T> gas,
+    const double* __restrict__ dt_dev, double dx, int first_order, int ws, int* __restrict__ n_bad, CflOut cfl,
+    int segs) {
+  __shared__ Smem<T> sm;
+  __shared__ double cfl_slots[kCfl ? 2 * kCflHalfStride : 1];
+  set_dt(gas, dt_dev, dx);
+  if (kCfl && cfl.reset != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *cfl.reset = 0x7ff0000000000000ull;
+  const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
+  const LevelSource<T, unsigned int> src{level, geo, g % geo.ngx, (g / geo.ngx) % geo.ngy, g / (geo.ngx * geo.ngy)};
+  double* smax = nullptr;
+  if (kCfl) {
+    smax = cfl_slots + cfl_slot(threadIdx.x);
+    smax[0] = 0.0;
+    smax[kCflHalfStride] = 0.0;
+  }
+  const int bad = process_group<T, false>(src, level_out + int64_t(g) * 5 * 4096, gas, first_order, ws, sm, smax,
+                                          cfl.gamma, threadIdx.x, (T*)nullptr, nullptr, DefaultScheme(),
+                                          ZPart{lo, lo + n});
+  if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
+  // a segment lies in one z half; the per-patch output is complete only when
+  // it is that half (the launch asks for it with two segments at most)
+  if (kCfl)
+    cfl_epilogue(cfl_slots, cfl.c_cfl_dx, cfl.dt_patch != nullptr ? cfl.dt_patch + int64_t(g) * 8 : nullptr, cfl.dt_min,
+                 1.0, threadIdx.x, lo >> 3);
+}
+
+// The groups of every level of a batched launch, one workgroup per segment
+// (no queue: a launch this small has one round of workgroups).
+template <typename T, bool kCfl>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_batched_seg_kernel(
+    BatchArgs<T> args, Gas<T> gas, int first_order, int ws, int* __restrict__ n_bad, int segs) {
+  __shared__ Smem<T> sm;
+  __shared__ double cfl_slots[kCfl ? 2 * kCflHalfStride : 1];
+  if (kCfl && blockIdx.x == 0 && threadIdx.x < unsigned(args.n_levels) && args.lv[threadIdx.x].reset != nullptr)
+    *args.lv[threadIdx.x].reset = 0x7ff0000000000000ull;
+  const int item = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
+  int l = 0;
+  while (l + 1 < args.n_levels && item >= args.lv[l + 1].g_begin) ++l;
+  const BatchLevel<T>& L = args.lv[l];
+  const int g = item - int(L.g_begin);
+  gas.dtdx = L.dtdx;
+  gas.half_dtdx = L.half_dtdx;
+  if (L.dt_dev != nullptr) {
+    const double dt = *L.dt_dev * L.dt_scale;  // exact for a power-of-two scale
+    gas.dtdx = T(dt / L.dx);
+    gas.half_dtdx = T(0.5 * (dt / L.dx));
+  }
+  const LevelGeom& geo = L.geo;
+  const LevelSource<T, unsigned int> src{L.in, geo, g % geo.ngx, (g / geo.ngx) % geo.ngy, g / (geo.ngx * geo.ngy)};
+  double* smax = nullptr;
+  if (kCfl && (L.dt_min != nullptr || L.dt_patch != nullptr)) {
+    smax = cfl_slots + cfl_slot(threadIdx.x);
+    smax[0] = 0.0;
+    smax[kCflHalfStride] = 0.0;
+  }
+  const int bad = process_group<T, false>(src, L.out + int64_t(g) * 5 * 4096, gas, first_order, ws, sm, smax,
+                                          args.gamma, threadIdx.x, (T*)nullptr, nullptr, DefaultScheme(),
+                                          ZPart{lo, lo + n});
+  if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
+  if (kCfl && smax != nullptr)
+    cfl_epilogue(cfl_slots, L.c_cfl_dx, L.dt_patch != nullptr ? L.dt_patch + int64_t(g) * 8 : nullptr, L.dt_min,
+                 L.fold_scale, threadIdx.x, lo >> 3);
+}
+
+template <typename T, bool kFlux>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_padded_seg_kernel(
+    const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
+    int first_order, int ws, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
+  __shared__ Smem<T> sm;
+  set_dt(gas, dt_dev, dx);
+  const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
+  const int P = 16 + 2 * gh;
+  const PaddedSource<T> src{Upad + int64_t(g) * 5 * P * P * P, P, gh};
+  T* ff = kFlux ? face_flux + int64_t(g) * 9 * 5 * 256 : nullptr;
+  const int bad = process_group<T, false>(src, Uout + int64_t(g) * 5 * 4096, gas, first_order, ws, sm, nullptr, 0.0,
+                                          threadIdx.x, ff, nullptr, DefaultScheme(), ZPart{lo, lo + n});
+  if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
+}
+
+template <typename T, bool kFlux, int kChr, int kRoe>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_padded_ext_seg_kernel(
+    const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
+    ExtOpts o, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
+  __shared__ Smem<T> sm;
+  set_dt(gas, dt_dev, dx);
+  const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
+  const int P = 16 + 2 * gh;
+  const PaddedSource<T> src{Upad + int64_t(g) * 5 * P * P * P, P, gh};
+  T* ff = kFlux ? face_flux + int64_t(g) * 9 * 5 * 256 : nullptr;
+  const ExtSchemeT<kChr, kRoe> sch{o};
+  const int bad = process_group<T, false>(src, Uout + int64_t(g) * 5 * 4096, gas, o.first_order, o.ws, sm, nullptr,
+                                          0.0, threadIdx.x, ff, nullptr, sch, ZPart{lo, lo + n});
+  if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
+}
+
+template <typename T, bool kFlux>
+void launch_ext_seg(const T* U_pad, T* U_out, dim3 grid, int ghost, const Gas<T>& gas, const double* dt_dev, double dx,
+                    const ExtOpts& o, int* n_bad, hipStream_t stream, T* ff, int segs) {
+  const bool roe = o.solver == 1;
+  const dim3 block(kThreads);
+  if (o.chr) {
+    if (roe) hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 1, 1>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
+    else hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 1, 0>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
+  } else {
+    if (roe) hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 0, 1>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
+    else hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 0, 0>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
+  }
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_mhm_level_seg(const T* level, T* level_out, const LevelGeom& geo, const Gas<T>& gas,
+                                const double* dt_dev, double dx, int first_order, int ws, int* n_bad,
+                                const CflOut& cfl, int segs, hipStream_t stream) {
+  const dim3 grid(unsigned(geo.ngx * geo.ngy * geo.ngz * segs));
+  if (cfl.dt_min != nullptr || cfl.dt_patch != nullptr || cfl.reset != nullptr)
+    hipLaunchKernelGGL((mhm_level_seg_kernel<T, true>), grid, dim3(kThreads), 0, stream, level, level_out, geo, gas,
+                       dt_dev, dx, first_order, ws, n_bad, cfl, segs);
+  else
+    hipLaunchKernelGGL((mhm_level_seg_kernel<T, false>), grid, dim3(kThreads), 0, stream, level, level_out, geo, gas,
+                       dt_dev, dx, first_order, ws, n_bad, cfl, segs);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_mhm_batched_seg(const BatchArgs<T>& args, const Gas<T>& gas, int first_order, int ws, int* n_bad,
+                                  int segs, hipStream_t stream) {
+  const dim3 grid(unsigned(args.total * segs));
+  if (args.cfl)
+    hipLaunchKernelGGL((mhm_batched_seg_kernel<T, true>), grid, dim3(kThreads), 0, stream, args, gas, first_order, ws,
+                       n_bad, segs);
+  else
+    hipLaunchKernelGGL((mhm_batched_seg_kernel<T, false>), grid, dim3(kThreads), 0, stream, args, gas, first_order, ws,
+                       n_bad, segs);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_mhm_fwd_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
+                              const double* dt_dev, double dx, int first_order, int ws, int* n_bad,
+                              hipStream_t stream, T* face_flux, int segs) {
+  const dim3 grid(unsigned(n_groups * segs));
+  if (face_flux != nullptr)
+    hipLaunchKernelGGL((mhm_padded_seg_kernel<T, true>), grid, dim3(kThreads), 0, stream, U_pad, U_out, ghost, gas,
+                       dt_dev, dx, first_order, ws, n_bad, face_flux, segs);
+  else
+    hipLaunchKernelGGL((mhm_padded_seg_kernel<T, false>), grid, dim3(kThreads), 0, stream, U_pad, U_out, ghost, gas,
+                       dt_dev, dx, first_order, ws, n_bad, face_flux, segs);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_mhm_fwd_ext_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
+                                  const double* dt_dev, double dx, const ExtOpts& o, int* n_bad, hipStream_t stream,
+                                  T* face_flux, int segs) {
+  const dim3 grid(unsigned(n_groups * segs));
+  if (face_flux != nullptr)
+    launch_ext_seg<T, true>(U_pad, U_out, grid, ghost, gas, dt_dev, dx, o, n_bad, stream, face_flux, segs);
+  else
+    launch_ext_seg<T, false>(U_pad, U_out, grid, ghost, gas, dt_dev, dx, o, n_bad, stream, face_flux, segs);
+  return hipGetLastError();
+}
+
+#define GH_SEG_INST(T)                                                                                                \
+  template hipError_t launch_mhm_level_seg<T>(const T*, T*, const LevelGeom&, const Gas<T>&, const double*, double,   \
+                                              int, int, int*, const CflOut&, int, hipStream_t);                       \
+  template hipError_t launch_mhm_batched_seg<T>(const BatchArgs<T>&, const Gas<T>&, int, int, int*, int, hipStream_t); \
+  template hipError_t launch_mhm_fwd_seg<T>(const T*, T*, int, int, const Gas<T>&, const double*, double, int, int,   \
+                                            int*, hipStream_t, T*, int);                                              \
+  template hipError_t launch_mhm_fwd_ext_seg<T>(const T*, T*, int, int, const Gas<T>&, const double*, double,         \
+                                                const ExtOpts&, int*, hipStream_t, T*, int);
+GH_SEG_INST(double)
+GH_SEG_INST(float)
+#undef GH_SEG_INST
+
+}  // namespace gh
