@@ -324,6 +324,23 @@ typedef struct {
 int hydro_amr_fill_ghosts(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, const void* coarse_old_dev,
                           const void* coarse_new_dev, double a, const int32_t* bc_host, int32_t ghost, int32_t dtype,
                           void* U_pad_dev, void* stream);
+/* hydro_amr_advance -- one step of level `fine` with the default scheme words
+ *   (those of hydro_advance), reading the level's states (fine->U_dev, not
+ *   modified) directly: hydro_amr_fill_ghosts + hydro_advance_ext without the
+ *   padded copy of the level, the same results.  coarse, coarse_old_dev,
+ *   coarse_new_dev, a, bc_host, ghost (2..16): as for hydro_amr_fill_ghosts;
+ *   dt, dx, gamma, scheme, theta, n_bad_dev: as for hydro_advance.
+ *   U_out_dev      [G][5][16^3] new states; must not overlap the old ones
+ *   U_pad_dev      scratch [G][5][P^3]: only ghost cells that no sibling holds
+ *                  are written and read
+ *   face_flux_dev  [G][9][5][16][16], written as by hydro_advance_ext for every
+ *                  group with face_flux_all != 0, else for the groups with a
+ *                  side that no sibling shares (what the flux registers read)
+ *   Asynchronous on stream. */
+int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, const void* coarse_old_dev,
+                      const void* coarse_new_dev, double a, const int32_t* bc_host, int32_t ghost, int32_t dtype,
+                      double dt, double dx, double gamma, int32_t scheme, double theta, void* U_out_dev,
+                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, int32_t face_flux_all, void* stream);
 int hydro_amr_flux_accumulate(const hydro_amr_level_t* fine, const void* face_flux_dev, double weight,
                               const int32_t* bc_host, int32_t dtype, void* reg_dev, void* stream);
 int hydro_amr_restrict(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, int32_t dtype, void* stream);

@@ -12,7 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhydro.so")
 OBJ = os.path.join(ROOT, "_build")
 SOURCES = ["capi.hip", "mhm_fwd.hip", "mhm_fwd_g2.hip", "mhm_fwd_ext.hip", "mhm_seg.hip", "mhm_batched.hip", "mhm_adj.hip", "aux_kernels.hip", "scheme_ext.hip",
-           "march_step.hip", "march_ctu_plm.hip", "march_ctu_ppm.hip", "fallback.hip", "amr.hip"]
+           "march_step.hip", "march_ctu_plm.hip", "march_ctu_ppm.hip", "fallback.hip", "amr.hip",
+           "mhm_amr.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

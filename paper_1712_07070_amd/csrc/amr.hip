@@ -115,6 +115,87 @@ __global__ __launch_bounds__(256) void amr_fill_kernel(const T* __restrict__ Uf,
   }
 }
 
+// The cells of amr_fill that the default step reads and no sibling holds
+// (hydro_amr_advance), one workgroup per group, a thread per coarse cell
+// around the parent patch: two ghost layers are one layer of coarse cells, and
+// the 8 children of a coarse cell share its slopes.  A group with all its
+// siblings leaves at once.  The same arithmetic as amr_fill_kernel.
+template <typename T>
+__global__ __launch_bounds__(256) void amr_fill_open_kernel(AmrLevelArgs F, const T* __restrict__ Cold,
+                                                            const T* __restrict__ Cnew, LevelDev C, T a, AmrBc bc,
+                                                            int ghost, T* __restrict__ pad) {
+  __shared__ int sib[27];
+  __shared__ int open;
+  const int64_t g = blockIdx.x;
+  const int p0 = F.pos[3 * g], p1 = F.pos[3 * g + 1], p2 = F.pos[3 * g + 2];
+  const unsigned out = amr_outflow_faces(F, bc, p0, p1, p2);
+  if (threadIdx.x == 0) open = 0;
+  __syncthreads();
+  if (threadIdx.x < 27) {
+    sib[threadIdx.x] = amr_sibling(F, bc, p0, p1, p2, int(threadIdx.x));
+    if (sib[threadIdx.x] < 0) open = 1;
+  }
+  __syncthreads();
+  if (!open) return;
+  const int P = 16 + 2 * ghost;
+  const int64_t P3 = int64_t(P) * P * P;
+  const int M0 = 16 * C.n[0], M1 = 16 * C.n[1], M2 = 16 * C.n[2];
+  // the 488 coarse cells around the parent patch: two 10 x 10 layers, then the
+  // 36 of the rim of each of the 8 layers between
+  for (int i = threadIdx.x; i < 488; i += blockDim.x) {
+    int cx, cy, cz;
+    if (i < 200) {
+      cx = i % 10 - 1, cy = (i / 10) % 10 - 1, cz = i < 100 ? -1 : 8;
+    } else {
+      const int r = (i - 200) % 36;
+      cz = (i - 200) / 36;
+      cx = r < 20 ? r % 10 - 1 : (r & 1) ? 8 : -1;
+      cy = r < 20 ? (r < 10 ? -1 : 8) : (r - 20) >> 1;
+    }
+    const int kx = cx < 0 ? 0 : cx > 7 ? 2 : 1, ky = cy < 0 ? 0 : cy > 7 ? 2 : 1, kz = cz < 0 ? 0 : cz > 7 ? 2 : 1;
+    if (kz != 1 && kx != 1 && ky != 1) continue;  // corners are not read
+    if (sib[(kz * 3 + ky) * 3 + kx] >= 0) continue;
+    // beyond an outflow face the step reads the edge cell instead
+    if ((kx == 0 && (out & 1u)) || (kx == 2 && (out & 2u)) || (ky == 0 && (out & 4u)) || (ky == 2 && (out & 8u)) ||
+        (kz == 0 && (out & 16u)) || (kz == 2 && (out & 32u)))
+      continue;
+    const int c0 = wrap(8 * p0 + cx, M0, bc.v[0], bc.v[1]), c1 = wrap(8 * p1 + cy, M1, bc.v[2], bc.v[3]),
+              c2 = wrap(8 * p2 + cz, M2, bc.v[4], bc.v[5]);
+    auto at = [&](int dx, int dy, int dz, T u[5]) {
+      const int xx = wrap(c0 + dx, M0, bc.v[0], bc.v[1]);
+      const int yy = wrap(c1 + dy, M1, bc.v[2], bc.v[3]);
+      const int zz = wrap(c2 + dz, M2, bc.v[4], bc.v[5]);
+      const int64_t o =
+          int64_t(C.at(xx >> 4, yy >> 4, zz >> 4)) * 5 * 4096 + ((zz & 15) * 16 + (yy & 15)) * 16 + (xx & 15);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) u[q] = (T(1) - a) * Cold[o + q * 4096] + a * Cnew[o + q * 4096];
+    };
+    T U0[5], Um[5], Up[5], s0[5], s1[5], s2[5];
+    at(0, 0, 0, U0);
+    at(-1, 0, 0, Um);
+    at(1, 0, 0, Up);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) s0[q] = minmod2(U0[q] - Um[q], Up[q] - U0[q]);
+    at(0, -1, 0, Um);
+    at(0, 1, 0, Up);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) s1[q] = minmod2(U0[q] - Um[q], Up[q] - U0[q]);
+    at(0, 0, -1, Um);
+    at(0, 0, 1, Up);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) s2[q] = minmod2(U0[q] - Um[q], Up[q] - U0[q]);
+    T* d = pad + g * 5 * P3 + (int64_t(2 * cz + ghost) * P + (2 * cy + ghost)) * P + (2 * cx + ghost);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const T off0 = (c & 1) ? T(0.25) : T(-0.25), off1 = (c & 2) ? T(0.25) : T(-0.25),
+              off2 = (c & 4) ? T(0.25) : T(-0.25);
+#pragma unroll
+      for (int q = 0; q < 5; ++q)
+        d[q * P3 + ((c >> 2) * P + ((c >> 1) & 1)) * P + (c & 1)] = ((U0[q] + s0[q] * off0) + s1[q] * off1) + s2[q] * off2;
+    }
+  }
+}
+
 // Side s = 2 axis + high of fine group g: the group across it is missing (a
 // side on an outflow domain face has no interface).
 __device__ __forceinline__ bool interface_side(const LevelDev& F, int64_t g, int s, const Bc6& bc) {
@@ -232,6 +313,18 @@ hipError_t launch_amr_fill(const T* Uf, const AmrLevelArgs& F, const T* Cold, co
 }
 
 template <typename T>
+hipError_t launch_amr_fill_open(const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C, double a,
+                                const int bc[6], int ghost, T* pad, hipStream_t stream) {
+  if (F.G == 0) return hipSuccess;
+  if (F.G > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
+  AmrBc b;
+  for (int i = 0; i < 6; ++i) b.v[i] = bc[i];
+  hipLaunchKernelGGL(amr_fill_open_kernel<T>, dim3(unsigned(F.G)), dim3(256), 0, stream, F, Cold, Cnew, to_dev(C),
+                     T(a), b, ghost, pad);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_amr_accumulate(const AmrLevelArgs& F, const T* face_flux, double w, const int bc[6], T* R,
                                  hipStream_t stream) {
   if (F.G == 0) return hipSuccess;
@@ -260,6 +353,8 @@ hipError_t launch_amr_fixup(T* Uc, const AmrLevelArgs& C, const AmrLevelArgs& F,
 #define GH_AMR_INST(T)                                                                                             \
   template hipError_t launch_amr_fill<T>(const T*, const AmrLevelArgs&, const T*, const T*, const AmrLevelArgs&,    \
                                          double, const int*, int, T*, hipStream_t);                                 \
+  template hipError_t launch_amr_fill_open<T>(const AmrLevelArgs&, const T*, const T*, const AmrLevelArgs&, double, \
+                                              const int*, int, T*, hipStream_t);                                    \
   template hipError_t launch_amr_accumulate<T>(const AmrLevelArgs&, const T*, double, const int*, T*, hipStream_t); \
   template hipError_t launch_amr_restrict<T>(const T*, const AmrLevelArgs&, T*, const AmrLevelArgs&, hipStream_t);  \
   template hipError_t launch_amr_fixup<T>(T*, const AmrLevelArgs&, const AmrLevelArgs&, const T*, const T*, double, \

@@ -835,6 +835,48 @@ int hydro_amr_fill_ghosts(const hydro_amr_level_t* fine, const hydro_amr_level_t
   return device_status(e);
 }
 
+int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, const void* coarse_old_dev,
+                      const void* coarse_new_dev, double a, const int32_t* bc_host, int32_t ghost, int32_t dtype,
+                      double dt, double dx, double gamma, int32_t scheme, double theta, void* U_out_dev,
+                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, int32_t face_flux_all, void* stream) {
+  if (!amr_level_ok(fine, true) || !bc_ok(bc_host) || ghost < 2 || ghost > 16 || U_pad_dev == nullptr ||
+      U_out_dev == nullptr || face_flux_dev == nullptr || (dtype != HYDRO_F64 && dtype != HYDRO_F32))
+    return HYDRO_EINVAL;
+  if (!finite_pos(dt) || !finite_pos(dx) || !(std::isfinite(gamma) && gamma > 1.0) || !valid_scheme(scheme, theta))
+    return HYDRO_EINVAL;
+  gh::AmrLevelArgs C{};
+  if (coarse != nullptr) {
+    if (!amr_level_ok(coarse, false) || !amr_pair_ok(fine, coarse) || coarse_old_dev == nullptr ||
+        coarse_new_dev == nullptr || !(a >= 0.0 && a <= 1.0))
+      return HYDRO_EINVAL;
+    C = amr_args(coarse);
+  } else if (fine->n_groups != int64_t(fine->n[0]) * fine->n[1] * fine->n[2]) {
+    return HYDRO_EINVAL;  // only a level covering the domain needs no coarse level
+  }
+  const int64_t P = 16 + 2 * ghost, G = fine->n_groups;
+  const size_t es = dtype_size(dtype), ub = size_t(G) * 5 * 4096 * es, pb = size_t(G) * 5 * P * P * P * es,
+               fb = size_t(G) * 9 * 5 * 256 * es;
+  if (overlap(U_pad_dev, pb, fine->U_dev, ub) || overlap(U_out_dev, ub, fine->U_dev, ub) ||
+      overlap(U_out_dev, ub, U_pad_dev, pb) || overlap(face_flux_dev, fb, fine->U_dev, ub) ||
+      overlap(face_flux_dev, fb, U_out_dev, ub) || overlap(face_flux_dev, fb, U_pad_dev, pb))
+    return HYDRO_EINVAL;
+  const int first_order = (scheme & HYDRO_FIRST_ORDER) ? 1 : 0, ws = (scheme >> 8) & 3;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  auto go = [&](auto zero) -> hipError_t {
+    using T = decltype(zero);
+    if (coarse != nullptr) {  // a level without one covers the domain: no cell is missing
+      const hipError_t e = gh::launch_amr_fill_open(amr_args(fine), static_cast<const T*>(coarse_old_dev),
+                                                    static_cast<const T*>(coarse_new_dev), C, a, bc_host, ghost,
+                                                    static_cast<T*>(U_pad_dev), s);
+      if (e != hipSuccess) return e;
+    }
+    return gh::launch_mhm_amr(static_cast<const T*>(fine->U_dev), static_cast<T*>(U_out_dev), amr_args(fine),
+                              static_cast<const T*>(U_pad_dev), ghost, bc_host, make_gas<T>(gamma, theta, dt, dx),
+                              first_order, ws, n_bad_dev, static_cast<T*>(face_flux_dev), int(face_flux_all), s);
+  };
+  return device_status(dtype == HYDRO_F64 ? go(0.0) : go(0.0f));
+}
+
 int hydro_amr_flux_accumulate(const hydro_amr_level_t* fine, const void* face_flux_dev, double weight,
                               const int32_t* bc_host, int32_t dtype, void* reg_dev, void* stream) {
   if (!amr_level_ok(fine, false) || !bc_ok(bc_host) || face_flux_dev == nullptr || reg_dev == nullptr ||

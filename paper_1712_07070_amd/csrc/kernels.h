@@ -214,6 +214,37 @@ struct AmrLevelArgs {
   int64_t G;
   int n[3];
 };
+struct AmrBc {
+  int v[6];
+};
+// Group of the level's lattice at offset class t = (dz*3 + dy)*3 + dx (0, 1, 2:
+// below, at, above) from position p, -1 if the level has none there or the
+// domain ends (outflow).
+__device__ __forceinline__ int amr_sibling(const AmrLevelArgs& F, const AmrBc& bc, int p0, int p1, int p2, int t) {
+  auto along = [](int p, int n, int lo, int hi) {
+    return p < 0 ? (lo != 0 ? -1 : p + n) : p >= n ? (hi != 0 ? -1 : p - n) : p;
+  };
+  const int x = along(p0 + t % 3 - 1, F.n[0], bc.v[0], bc.v[1]);
+  const int y = along(p1 + (t / 3) % 3 - 1, F.n[1], bc.v[2], bc.v[3]);
+  const int z = along(p2 + t / 9 - 1, F.n[2], bc.v[4], bc.v[5]);
+  return (x < 0 || y < 0 || z < 0) ? -1 : F.map[(int64_t(z) * F.n[1] + y) * F.n[0] + x];
+}
+// Bits x-, x+, y-, y+, z-, z+: the group at p touches that face of the domain
+// and it is an outflow face.
+__device__ __forceinline__ unsigned amr_outflow_faces(const AmrLevelArgs& F, const AmrBc& bc, int p0, int p1, int p2) {
+  return unsigned(bc.v[0] != 0 && p0 == 0) | unsigned(bc.v[1] != 0 && p0 == F.n[0] - 1) << 1 |
+         unsigned(bc.v[2] != 0 && p1 == 0) << 2 | unsigned(bc.v[3] != 0 && p1 == F.n[1] - 1) << 3 |
+         unsigned(bc.v[4] != 0 && p2 == 0) << 4 | unsigned(bc.v[5] != 0 && p2 == F.n[2] - 1) << 5;
+}
+// Padded blocks: only the cells the default step reads where no sibling is.
+template <typename T>
+hipError_t launch_amr_fill_open(const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C, double a,
+                                const int bc[6], int ghost, T* pad, hipStream_t stream);
+// The default step of a level from its states and those blocks (mhm_amr.hip).
+template <typename T>
+hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* pad, int ghost, const int bc[6],
+                          const Gas<T>& gas, int first_order, int ws, int* n_bad, T* face_flux, int ff_all,
+                          hipStream_t stream);
 template <typename T>
 hipError_t launch_amr_fill(const T* Uf, const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C,
                            double a, const int bc[6], int ghost, T* pad, hipStream_t stream);

@@ -194,12 +194,12 @@ __device__ __forceinline__ void adj_col_init(AdjCol<T, kI>& c, const Src& src, i
   c.col = src.col(cx, cy);
   if (kI) {
     T W[5];
-    load_prim(src, c.col, -2, gas, W);
+    load_prim<kI>(src, c.col, -2, gas, W);
 #pragma unroll
     for (int q = 0; q < 5; ++q) sm.P[pslot(-2)][q][pidx(cx, cy)] = W[q];
   }
-  load_prim(src, c.col, -1, gas, c.Wp);  // published as plane -1 by the first iteration
-  load_cons(src, c.col, 0, c.Un);
+  load_prim<kI>(src, c.col, -1, gas, c.Wp);  // published as plane -1 by the first iteration
+  load_cons<kI>(src, c.col, 0, c.Un);
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
     c.gRx[q] = c.gRy[q] = c.gRz[q] = T(0);
@@ -219,7 +219,7 @@ __device__ __forceinline__ void adj_col_publish(AdjCol<T, kI>& c, const Src& src
   for (int q = 0; q < 5; ++q) sm.P[pslot(k)][q][pidx(c.cx, c.cy)] = c.Wp[q];
   cons_to_prim(c.Un, gas, c.Wp);
   asm volatile("" ::: "memory");
-  load_cons(src, c.col, k + 2 <= c.zhi ? k + 2 : c.zhi, c.Un);
+  load_cons<kI>(src, c.col, k + 2 <= c.zhi ? k + 2 : c.zhi, c.Un);
 }
 
 // F2: half-step states of plane k and the z-face (k-1 | k) VJP (kFwd); then
@@ -507,8 +507,8 @@ __device__ __forceinline__ void adjoint_fused(const Src& src, const T* __restric
   T Uo[5], Ue[5];  // halo role: 2-deep and edge column, plane k (in flight)
   if (halo || hrev) adj_col_init(ch, src, hx, hy, gas, sm);
   if (halo) {
-    load_cons(src, col_out, 0, Uo);
-    load_cons(src, col_edge, 0, Ue);
+    load_cons<false>(src, col_out, 0, Uo);
+    load_cons<false>(src, col_edge, 0, Ue);
   }
 
   for (int k = -1; k <= 17; ++k) {
@@ -523,8 +523,8 @@ __device__ __forceinline__ void adjoint_fused(const Src& src, const T* __restric
           cons_to_prim(Ue, gas, We);
           asm volatile("" ::: "memory");
           const int kn = k + 1 > 15 ? 15 : k + 1;
-          load_cons(src, col_out, kn, Uo);
-          load_cons(src, col_edge, kn, Ue);
+          load_cons<false>(src, col_out, kn, Uo);
+          load_cons<false>(src, col_edge, kn, Ue);
 #pragma unroll
           for (int q = 0; q < 5; ++q) sm.P[sk][q][pidx(ox, oy)] = Wo[q];
           if (has_edge) {
@@ -620,8 +620,8 @@ __device__ __forceinline__ void split_col_init(SplitCol<T, kI>& c, const Src& sr
   c.xface16 = !kI && cx == 16;
   c.yface16 = !kI && cy == 16;
   c.col = src.col(cx, cy);
-  if (kI) load_prim(src, c.col, -2, gas, c.Wm);
-  load_prim(src, c.col, -1, gas, c.Wc);
+  if (kI) load_prim<kI>(src, c.col, -2, gas, c.Wm);
+  load_prim<kI>(src, c.col, -1, gas, c.Wc);
 #pragma unroll
   for (int q = 0; q < 5; ++q) c.A0[q] = c.A1[q] = c.A2[q] = T(0);
 }
@@ -629,7 +629,7 @@ __device__ __forceinline__ void split_col_init(SplitCol<T, kI>& c, const Src& sr
 template <typename T, bool kI, class Src>
 __device__ __forceinline__ void split_col_publish(SplitCol<T, kI>& c, const Src& src, int k, const Gas<T>& gas,
                                                   T (*P)[kPW * kPW]) {
-  if (k + 1 <= c.zhi) load_prim(src, c.col, k + 1, gas, c.Wp);
+  if (k + 1 <= c.zhi) load_prim<kI>(src, c.col, k + 1, gas, c.Wp);
 #pragma unroll
   for (int q = 0; q < 5; ++q) P[q][pidx(c.cx, c.cy)] = c.Wc[q];
 }
@@ -649,11 +649,11 @@ __device__ __forceinline__ void publish_outer(const Src& src, int k, int64_t col
                                               int64_t col_edge, int ex, int ey, const Gas<T>& gas,
                                               T (*P)[kPW * kPW]) {
   T Wo[5];
-  load_prim(src, col_out, k, gas, Wo);
+  load_prim<false>(src, col_out, k, gas, Wo);
 #pragma unroll
   for (int q = 0; q < 5; ++q) P[q][pidx(ox, oy)] = Wo[q];
   if (has_edge) {
-    load_prim(src, col_edge, k, gas, Wo);
+    load_prim<false>(src, col_edge, k, gas, Wo);
 #pragma unroll
     for (int q = 0; q < 5; ++q) P[q][pidx(ex, ey)] = Wo[q];
   }

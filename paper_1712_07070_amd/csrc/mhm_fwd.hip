@@ -54,6 +54,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kWaves
                                                               int* __restrict__ n_bad, T* __restrict__ face_flux,
                                                               unsigned* __restrict__ record = nullptr) {
   __shared__ Smem<T> sm;
+  __shared__ T stage[kFlux ? kFluxStage : 1];
   set_dt(gas, dt_dev, dx);
   const int P = 16 + 2 * gh;
   const int64_t P3 = int64_t(P) * P * P;
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kWaves
   T* ff = kFlux ? face_flux + int64_t(blockIdx.x) * 9 * 5 * 256 : nullptr;
   unsigned* rec = kRec ? record + blockIdx.x : nullptr;
   const int bad = process_group<T, (kWaves >= 4)>(src, Uout + int64_t(blockIdx.x) * 5 * 4096, gas, first_order, ws, sm, nullptr,
-                                   0.0, threadIdx.x, ff, rec);
+                                   0.0, threadIdx.x, ff, rec, DefaultScheme(), ZAll(), stage);
   if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
 }
 

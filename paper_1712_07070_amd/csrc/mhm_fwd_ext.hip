@@ -17,6 +17,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kWaves
     const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
     ExtOpts o, int* __restrict__ n_bad, T* __restrict__ face_flux) {
   __shared__ Smem<T> sm;
+  __shared__ T stage[kFlux ? kFluxStage : 1];
   set_dt(gas, dt_dev, dx);
   const int P = 16 + 2 * gh;
   const int64_t P3 = int64_t(P) * P * P;
@@ -24,7 +25,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kWaves
   T* ff = kFlux ? face_flux + int64_t(blockIdx.x) * 9 * 5 * 256 : nullptr;
   const ExtSchemeT<kChr, kRoe> sch{o};
   const int bad = process_group<T, (kWaves >= 4)>(src, Uout + int64_t(blockIdx.x) * 5 * 4096, gas, o.first_order,
-                                                  o.ws, sm, nullptr, 0.0, threadIdx.x, ff, nullptr, sch);
+                                                  o.ws, sm, nullptr, 0.0, threadIdx.x, ff, nullptr, sch, ZAll(), stage);
   if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
 }
 

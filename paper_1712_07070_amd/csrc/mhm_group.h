@@ -64,7 +64,8 @@ struct LevelSource {
   __device__ Off fstride() const { return 4096; }
 };
 
-template <typename T, class Src>
+// kI: an interior column (x and y inside the group for every lane).
+template <bool kI, typename T, class Src>
 __device__ __forceinline__ void load_cons(const Src& src, typename Src::Off col, int z, T U[5]) {
   const typename Src::Off o = col + src.plane(z);
   const typename Src::Off fs = src.fstride();
@@ -72,10 +73,57 @@ __device__ __forceinline__ void load_cons(const Src& src, typename Src::Off col,
   for (int q = 0; q < 5; ++q) U[q] = src.base[o + q * fs];
 }
 
-template <typename T, class Src>
+// A group of an AMR level: cells of the group and of the siblings around it
+// are read from the level's states, cells where no sibling is from the
+// group's padded block (interpolated there beforehand, only those).  A
+// column's "offset" holds its coordinates, (y + 2) * 32 + (x + 2), clamped
+// where the domain ends with outflow, as z is at the load.
+template <typename T>
+struct AmrSource {
+  using Off = unsigned int;
+  const T* U;          // states of the level
+  const T* pad;        // this group's padded block
+  const int* sib;      // LDS: sibling groups, [z][y][x] class (below, in, above), -1 where absent
+  int below, self, above;  // sib of the centre column
+  int P, gh;
+  unsigned out;        // bits x-, x+, y-, y+, z-, z+: the group touches an outflow face of the domain
+  static __device__ __forceinline__ int clamp(int i, unsigned lo, unsigned hi) {
+    return (i < 0 && lo) ? 0 : (i > 15 && hi) ? 15 : i;
+  }
+  __device__ Off col(int x, int y) const {
+    return unsigned((clamp(y, out & 4u, out & 8u) + 2) * 32 + clamp(x, out & 1u, out & 2u) + 2);
+  }
+};
+template <bool kI, typename T>
+__device__ __forceinline__ void load_cons(const AmrSource<T>& src, unsigned int col, int z, T U[5]) {
+  const int zc = AmrSource<T>::clamp(z, src.out & 16u, src.out & 32u);
+  const int x = int(col & 31u) - 2, y = int(col >> 5) - 2, cz = (zc + 16) >> 4;
+  const unsigned P3 = unsigned(src.P) * src.P * src.P;
+  const unsigned in = unsigned((zc & 15) * 256 + (y & 15) * 16 + (x & 15));
+  const unsigned at = unsigned(((zc + src.gh) * src.P + (y + src.gh)) * src.P + (x + src.gh));
+  // members read before they are selected from: a select of their addresses
+  // would keep the source in memory
+  const T *Us = src.U, *pad = src.pad;
+  if constexpr (kI) {
+    const int s0 = src.below, s1 = src.self, s2 = src.above;
+    const int s = cz == 0 ? s0 : cz == 1 ? s1 : s2;  // uniform
+    const T* b = s >= 0 ? Us + int64_t(s) * (5 * 4096) : pad;
+    const unsigned o = s >= 0 ? in : at, fs = s >= 0 ? 4096u : P3;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) U[q] = b[o + q * fs];
+  } else {
+    const int s = src.sib[cz * 9 + ((y + 16) >> 4) * 3 + ((x + 16) >> 4)];
+    const T* b = s >= 0 ? Us + (int64_t(s) * (5 * 4096) + in) : pad + at;
+    const unsigned fs = s >= 0 ? 4096u : P3;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) U[q] = b[q * fs];
+  }
+}
+
+template <bool kI, typename T, class Src>
 __device__ __forceinline__ void load_prim(const Src& src, typename Src::Off col, int z, const Gas<T>& g, T W[5]) {
   T U[5];
-  load_cons(src, col, z, U);
+  load_cons<kI>(src, col, z, U);
   cons_to_prim(U, g, W);
 }
 
@@ -251,9 +299,9 @@ __device__ __forceinline__ void fwd_col_init(FwdCol<T, kI, typename Src::Off>& c
   c.xface16 = !kI && cx == 16;
   c.yface16 = !kI && cy == 16;
   c.col = src.col(cx, cy);
-  if (kI) load_prim(src, c.col, zr.lo - 2, gas, c.Wm);
-  load_prim(src, c.col, zr.lo - 1, gas, c.Wc);
-  load_cons(src, c.col, zr.lo, c.Un);
+  if (kI) load_prim<kI>(src, c.col, zr.lo - 2, gas, c.Wm);
+  load_prim<kI>(src, c.col, zr.lo - 1, gas, c.Wc);
+  load_cons<kI>(src, c.col, zr.lo, c.Un);
 }
 
 // Next plane of the column (prefetched one iteration ahead); publish plane k.
@@ -268,7 +316,7 @@ __device__ __forceinline__ void fwd_col_publish(FwdCol<T, kI, typename Src::Off>
   // and wait for the load that is meant to stay in flight.
   cons_to_prim(c.Un, gas, c.Wp);
   asm volatile("" ::: "memory");
-  load_cons(src, c.col, k + 2 <= zhi ? k + 2 : zhi, c.Un);
+  load_cons<kI>(src, c.col, k + 2 <= zhi ? k + 2 : zhi, c.Un);
 #pragma unroll
   for (int q = 0; q < 5; ++q) sm.P[q][sm.pi(c.cx, c.cy)] = c.Wc[q];
 }
@@ -295,7 +343,7 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
   // U^n of plane k-1 for its update at the end of this phase, issued first
   // so that the load's latency overlaps the half step and the z-face solve
   T Uold[5];
-  if (kI && k > zr.lo) load_cons(src, c.col, k - 1, Uold);
+  if (kI && k > zr.lo) load_cons<kI>(src, c.col, k - 1, Uold);
   // x/y flux differences of plane k-1 (fluxes written last iteration)
   T acc[5];
   if (kI && k > zr.lo) {
@@ -377,7 +425,7 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
 // y face.
 template <typename T, bool kI, typename Off, int kL, class Sch, class Z>
 __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>& c, int k, const Gas<T>& gas, int ws, Smem<T, kL>& sm,
-                                             T* __restrict__ ff, unsigned* rec, const Z& zr) {
+                                             unsigned* rec, const Z& zr) {
   if (!kI || k < zr.lo || k >= zr.hi) return 0;
   const int cx = c.cx, cy = c.cy;
   T Lx[5], Fx[5], Ly[5], Fy[5];
@@ -392,19 +440,39 @@ __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>&
     sm.F[0][q][fxidx(cx, cy)] = Fx[q];
     sm.F[1][q][fyidx(cx, cy)] = Fy[q];
   }
-  if (ff != nullptr && (cx & 7) == 0) {
-    // x faces at x = 0, 8: plane x/8, entry z*16 + y
-    T* o = ff + (cx >> 3) * 5 * 256 + k * 16 + cy;
-#pragma unroll
-    for (int q = 0; q < 5; ++q) o[q * 256] = Fx[q];
-  }
-  if (ff != nullptr && (cy & 7) == 0) {
-    // y faces at y = 0, 8: plane 3 + y/8, entry x*16 + z
-    T* o = ff + (3 + (cy >> 3)) * 5 * 256 + cx * 16 + k;
-#pragma unroll
-    for (int q = 0; q < 5; ++q) o[q * 256] = Fy[q];
-  }
   return bad;
+}
+
+// Patch-boundary face fluxes of plane k from the flux arrays: axis 0 the x
+// faces at x = 0, 8, 16 (plane x/8 of ff, entry z*16 + y), axis 1 the y faces at
+// y = 0, 8, 16 (plane 3 + y/8, entry x*16 + z).  One wave copies an axis, in the
+// next plane's first phase: the plain waves 1 and 3, which the others wait
+// for least.  The y planes run along z, so a plane of the march holds one
+// entry of each of their rows: up to 8 planes wait in LDS (stage, kFluxStage
+// elements) and are stored together.  Stored by the threads that solve the
+// faces, a few lanes of every wave at a time, the fluxes cost a third of the
+// step (AMR level step 694 us against 521 without fluxes; by one wave per
+// axis 641, staged 586).
+constexpr int kFluxStage = 8 * 240;
+template <typename T, int kL>
+__device__ __forceinline__ void put_face_fluxes(int axis, int lane, int k, bool last, int first, const Smem<T, kL>& sm,
+                                                T* __restrict__ ff, T* stage) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int v = j * 64 + lane, pq = v >> 4, i = v & 15;  // pq = 5 (coordinate / 8) + field
+    if (v >= 240) break;
+    const int p = pq / 5, q = pq - 5 * p;
+    if (axis == 0) ff[pq * 256 + k * 16 + i] = sm.F[0][q][fxidx(8 * p, i)];
+    else stage[(k & 7) * 240 + v] = sm.F[1][q][fyidx(i, 8 * p)];
+  }
+  if (axis == 1 && ((k & 7) == 7 || last)) {
+    // planes k0 .. k of each row (the same lane stored them)
+    const int k0 = (k & 8) > first ? (k & 8) : first;
+    for (int v = lane; v < 240; v += 64) {
+      T* o = ff + (15 + (v >> 4)) * 256 + (v & 15) * 16;
+      for (int z = k0; z <= k; ++z) o[z] = stage[(z & 7) * 240 + v];
+    }
+  }
 }
 
 // The 32 last faces of plane k (x = 16 for lanes 0..15 at y = lane, y = 16
@@ -415,7 +483,7 @@ __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>&
 // H; this pass runs on another wave, which has no halo work.
 template <typename T, int kL, class Sch, class Z>
 __device__ __forceinline__ int last_faces(const Sch& sch, int lane, int k, const Gas<T>& gas, int ws, Smem<T, kL>& sm,
-                                          T* __restrict__ ff, unsigned* rec, const Z& zr) {
+                                          unsigned* rec, const Z& zr) {
   if (k < zr.lo || k >= zr.hi || lane >= 32) return 0;
   const bool yf = lane >= 16;
   const int i = lane & 15;
@@ -443,15 +511,6 @@ __device__ __forceinline__ int last_faces(const Sch& sch, int lane, int k, const
   Fb[2 * 17 * 16] = yf ? F[1] : F[2];
   Fb[3 * 17 * 16] = yf ? F[2] : F[3];
   Fb[4 * 17 * 16] = F[4];
-  if (ff != nullptr) {
-    // x = 16: plane 2, entry z*16 + y; y = 16: plane 5, entry x*16 + z
-    T* o = ff + (yf ? 5 * 5 * 256 + i * 16 + k : 2 * 5 * 256 + k * 16 + i);
-    o[0] = F[0];
-    o[1 * 256] = yf ? F[3] : F[1];
-    o[2 * 256] = yf ? F[1] : F[2];
-    o[3 * 256] = yf ? F[2] : F[3];
-    o[4 * 256] = F[4];
-  }
   return bad;
 }
 
@@ -473,7 +532,7 @@ enum WaveRole { kRoleHalo = 0, kRoleLastFaces = 1, kRolePlain = 2 };
 template <typename T, class Src, int kRole, int kUnroll, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas, int first_order,
                                            int ws, Smem<T, kL>& sm, double* smax, double gamma_d, int tid,
-                                           T* __restrict__ ff, unsigned* rec, const Z& zr) {
+                                           T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage) {
   // halo role: side 0..3 = x-, x+, y-, y+; the column two cells out; lanes
   // 0..3 also one of the 4 edge columns
   const int lane = tid & 63;
@@ -494,8 +553,8 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
     col_out = src.col(ox, oy);
     col_edge = src.col(has_edge ? ex : ox, has_edge ? ey : oy);  // lanes without an edge re-read their 2-deep column
     fwd_col_init(ch, src, hx, hy, gas, zr);
-    load_cons(src, col_out, zr.lo, Uo);
-    load_cons(src, col_edge, zr.lo, Ue);
+    load_cons<false>(src, col_out, zr.lo, Uo);
+    load_cons<false>(src, col_edge, zr.lo, Ue);
   }
   int bad = 0;
 
@@ -512,8 +571,8 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
       cons_to_prim(Ue, gas, We);
       asm volatile("" ::: "memory");
       const int kn = k + 1 < zr.lo ? zr.lo : (k + 1 >= zr.hi ? zr.hi - 1 : k + 1);
-      load_cons(src, col_out, kn, Uo);
-      load_cons(src, col_edge, kn, Ue);
+      load_cons<false>(src, col_out, kn, Uo);
+      load_cons<false>(src, col_edge, kn, Ue);
       if (k >= zr.lo && k < zr.hi) {
 #pragma unroll
         for (int q = 0; q < 5; ++q) sm.P[q][sm.pi(ox, oy)] = Wo[q];
@@ -526,13 +585,15 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
     __syncthreads();
 
     // ---- half-step face states of plane k; z-face and update of plane k-1
+    if (kRole == kRolePlain && ff != nullptr && k > zr.lo)
+      put_face_fluxes(tid >> 7, lane, k - 1, k == zr.hi, zr.lo, sm, ff, ff_stage);
     bad += fwd_col_states(sch, ci, src, out, k, gas, first_order, ws, sm, smax, gamma_d, ff, rec, zr);
     if (kHalo) bad += fwd_col_states(sch, ch, src, out, k, gas, first_order, ws, sm, nullptr, gamma_d, (T*)nullptr, rec, zr);
     __syncthreads();
 
     // ---- x and y faces of plane k
-    bad += fwd_col_faces(sch, ci, k, gas, ws, sm, ff, rec, zr);
-    if (kRole == kRoleLastFaces) bad += last_faces(sch, lane, k, gas, ws, sm, ff, rec, zr);
+    bad += fwd_col_faces(sch, ci, k, gas, ws, sm, rec, zr);
+    if (kRole == kRoleLastFaces) bad += last_faces(sch, lane, k, gas, ws, sm, rec, zr);
 
     fwd_col_shift(ci);
     if (kHalo) fwd_col_shift(ch);
@@ -548,7 +609,8 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 // fluxes of the faces on the patch boundaries (normal coordinate 0, 8, 16 of
 // each axis) to ff as [9][5][256]: plane 3 axis + k holds the faces at 8 k,
 // entry b * 16 + a with (a, b) the transverse coordinates in cyclic order
-// (the flux registers of coarse-fine coupling).  `tid` is the thread's index in the
+// (the flux registers of coarse-fine coupling); ff_stage: kFluxStage elements of
+// LDS for it.  `tid` is the thread's index in the
 // workgroup (a loop over groups passes it opaque, so that the compiler keeps
 // thread-derived addresses out of the loop's live set).  Wave 0 runs the
 // march with the halo roles, wave 2 with the last faces, waves 1 and 3 with
@@ -566,7 +628,7 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 template <typename T, bool kPrio, class Src, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas,
                                            int first_order, int ws, Smem<T, kL>& sm, double* smax, double gamma_d,
-                                           int tid, T* __restrict__ ff, unsigned* rec, const Z& zr) {
+                                           int tid, T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Two planes per loop iteration, so that the register rotation of a
   // column's planes (Wm <- Wc <- Wp, z-face state and flux) becomes renaming
@@ -584,29 +646,29 @@ __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __
   }
   if constexpr (std::is_same<Z, ZPart>::value) {
     // a z segment: few planes, one per loop iteration, one copy
-    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
-    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
   } else if constexpr (!std::is_same<Sch, DefaultScheme>::value) {
     // the other words: one copy (their options are run-time anyway), one
     // plane per loop iteration
-    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
-    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
   } else {
     if (first_order == 0) {
-      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
       if (wave == 2)
-        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
-      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
     }
     if (wave == 0)
-      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
-    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr);
+      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
   }
 }
 
@@ -618,13 +680,13 @@ __device__ __forceinline__ int process_group(const Src& src, T* __restrict__ out
                                              int first_order, int ws, Smem<T, kL>& sm, double* smax,
                                              double gamma_d, int tid = threadIdx.x, T* __restrict__ ff = nullptr,
                                              unsigned* __restrict__ rec_out = nullptr, const Sch& sch = Sch(),
-                                             const Z& zr = Z()) {
+                                             const Z& zr = Z(), T* ff_stage = nullptr) {
   if (rec_out == nullptr)
-    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr, zr);
+    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr, zr, ff_stage);
   __shared__ unsigned grp_rec;
   if (tid == 0) grp_rec = 0u;  // the march's first barrier orders this before any XOR
   unsigned h = 2166136261u ^ (unsigned(tid) * 0x9E3779B9u);
-  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h, zr);
+  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h, zr, ff_stage);
   atomicXor(&grp_rec, h);
   __syncthreads();
   if (tid == 0) *rec_out = grp_rec;

@@ -87,13 +87,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
     const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
     int first_order, int ws, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
   __shared__ Smem<T> sm;
+  __shared__ T stage[kFlux ? kFluxStage : 1];
   set_dt(gas, dt_dev, dx);
   const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
   const int P = 16 + 2 * gh;
   const PaddedSource<T> src{Upad + int64_t(g) * 5 * P * P * P, P, gh};
   T* ff = kFlux ? face_flux + int64_t(g) * 9 * 5 * 256 : nullptr;
   const int bad = process_group<T, false>(src, Uout + int64_t(g) * 5 * 4096, gas, first_order, ws, sm, nullptr, 0.0,
-                                          threadIdx.x, ff, nullptr, DefaultScheme(), ZPart{lo, lo + n});
+                                          threadIdx.x, ff, nullptr, DefaultScheme(), ZPart{lo, lo + n}, stage);
   if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
 }
 
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
     const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
     ExtOpts o, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
   __shared__ Smem<T> sm;
+  __shared__ T stage[kFlux ? kFluxStage : 1];
   set_dt(gas, dt_dev, dx);
   const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
   const int P = 16 + 2 * gh;
@@ -109,7 +111,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
   T* ff = kFlux ? face_flux + int64_t(g) * 9 * 5 * 256 : nullptr;
   const ExtSchemeT<kChr, kRoe> sch{o};
   const int bad = process_group<T, false>(src, Uout + int64_t(g) * 5 * 4096, gas, o.first_order, o.ws, sm, nullptr,
-                                          0.0, threadIdx.x, ff, nullptr, sch, ZPart{lo, lo + n});
+                                          0.0, threadIdx.x, ff, nullptr, sch, ZPart{lo, lo + n}, stage);
   if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
 }
 

@@ -92,6 +92,7 @@ def load():
         "hydro_advance_level_fallback": (i32, [P, P, P, i32, i32, i32, P, i32, f64, f64, f64, f64, f64, i32, f64,
                                                P, i64, P, P]),
         "hydro_amr_fill_ghosts": (i32, [P, P, P, P, f64, P, i32, i32, P, P]),
+        "hydro_amr_advance": (i32, [P, P, P, P, f64, P, i32, i32, f64, f64, f64, i32, f64, P, P, P, P, i32, P]),
         "hydro_amr_flux_accumulate": (i32, [P, P, f64, P, i32, P, P]),
         "hydro_amr_restrict": (i32, [P, P, i32, P]),
         "hydro_amr_fixup": (i32, [P, P, P, P, f64, P, i32, P]),
@@ -1028,9 +1029,10 @@ class AmrSolver:
     level l takes two steps of dt_l / 2 ... down the hierarchy, 2^l steps per
     coarse step; Sec. 2.2 restriction and flux fix-up; Sec. 3.2 ghost zones
     from siblings or interpolated from the coarse level).  Every operation is
-    one of the library's kernels: hydro_amr_fill_ghosts, hydro_advance_ext
-    (with its patch-boundary face fluxes), hydro_amr_flux_accumulate,
-    hydro_amr_restrict and hydro_amr_fixup.
+    one of the library's kernels: hydro_amr_advance for the default scheme words,
+    hydro_amr_fill_ghosts and hydro_advance_ext for the others (with the
+    patch-boundary face fluxes), hydro_amr_flux_accumulate, hydro_amr_restrict
+    and hydro_amr_fixup.
 
     positions[l]: int [G_l, 3] group positions on level l's lattice (n0 * 2^l
     per axis); states[l]: [G_l, 5, 16, 16, 16] device tensors (advanced in
@@ -1046,7 +1048,11 @@ class AmrSolver:
         self.scheme, self.theta, self.ghost = int(scheme), float(theta), int(ghost)
         self.U = list(states)
         dtype, device = self.U[0].dtype, self.U[0].device
-        self.maps, self.pos, self.pad, self.work, self.flux, self.old, self.reg = [], [], [], [], [], [], []
+        self.maps, self.pos, self.pad, self.work, self.flux, self.alt, self.reg = [], [], [], [], [], [], []
+        # the default words step a level from its own storage (hydro_amr_advance),
+        # alternating between the caller's tensor and `alt`
+        self.direct = (self.scheme & ~(WAVESPEED_DAVIS | FIRST_ORDER)) == SCHEME_MHM_PLM_HLLC
+        self.cur = [0] * self.nl
         maps_np = []
         for l, p in enumerate(positions):
             p = np.ascontiguousarray(p, np.int32).reshape(-1, 3)
@@ -1071,7 +1077,7 @@ class AmrSolver:
             self.pad.append(torch.empty((G, 5, P, P, P), dtype=dtype, device=device))
             self.work.append(ext_workspace(G, self.ghost, dtype, self.scheme, device))
             self.flux.append(torch.empty((G, 9, 5, 16, 16), dtype=dtype, device=device))
-            self.old.append(torch.empty_like(self.U[l]) if l + 1 < self.nl else None)
+            self.alt.append(torch.empty_like(self.U[l]) if self.direct or l + 1 < self.nl else None)
             self.reg.append(torch.zeros((G, 6, 5, 8, 8), dtype=dtype, device=device) if l > 0 else None)
         self.n_bad = torch.zeros(1, dtype=torch.int32, device=device)
         self._bcarr = (ctypes.c_int32 * 6)(*self.bc)
@@ -1114,17 +1120,36 @@ class AmrSolver:
         lib, s = load(), _stream()
         code = _dtype_code(self.U[l])
         dx = self.dx0 / 2 ** l
-        if l + 1 < self.nl:
-            self.old[l].copy_(self.U[l])
-        fine = self._lvl(l)
         coarse = self._lvl(l - 1) if l > 0 else None
-        st = lib.hydro_amr_fill_ghosts(ctypes.byref(fine), None if coarse is None else ctypes.byref(coarse),
-                                       None if cold is None else _dev(cold, "cold"),
-                                       None if cnew is None else _dev(cnew, "cnew"), float(a), self._bcarr,
-                                       self.ghost, code, _dev(self.pad[l], "pad"), s)
-        _check(st, "hydro_amr_fill_ghosts")
-        advance_ext(self.pad[l], dt, dx, self.gamma, self.scheme, self.theta, out=self.U[l], n_bad=self.n_bad,
-                    work=self.work[l], face_flux=self.flux[l])
+        cptr = None if coarse is None else ctypes.byref(coarse)
+        oldp = None if cold is None else _dev(cold, "cold")
+        newp = None if cnew is None else _dev(cnew, "cnew")
+        if self.direct:
+            # the old states stay where they are (level 0 takes one substep: they
+            # are copied aside, so that the new ones land in the caller's tensor)
+            if l == 0:
+                old, new = self.alt[0], self.U[0]
+                old.copy_(new)
+            else:
+                old, new = (self.U[l], self.alt[l]) if self.cur[l] == 0 else (self.alt[l], self.U[l])
+                self.cur[l] ^= 1
+            src = self._lvl(l, old)
+            st = lib.hydro_amr_advance(ctypes.byref(src), cptr, oldp, newp, float(a), self._bcarr, self.ghost, code,
+                                       float(dt), float(dx), self.gamma, self.scheme, self.theta, _dev(new, "new"),
+                                       _dev(self.pad[l], "pad"), _dev(self.n_bad, "n_bad"),
+                                       _dev(self.flux[l], "flux"), int(l + 1 < self.nl), s)
+            _check(st, "hydro_amr_advance")
+        else:
+            old, new = self.alt[l], self.U[l]
+            if l + 1 < self.nl:
+                old.copy_(new)
+            fine = self._lvl(l)
+            st = lib.hydro_amr_fill_ghosts(ctypes.byref(fine), cptr, oldp, newp, float(a), self._bcarr, self.ghost,
+                                           code, _dev(self.pad[l], "pad"), s)
+            _check(st, "hydro_amr_fill_ghosts")
+            advance_ext(self.pad[l], dt, dx, self.gamma, self.scheme, self.theta, out=new, n_bad=self.n_bad,
+                        work=self.work[l], face_flux=self.flux[l])
+        fine = self._lvl(l, new)
         if R_parent is not None:
             st = lib.hydro_amr_flux_accumulate(ctypes.byref(fine), _dev(self.flux[l], "flux"), 0.5, self._bcarr, code,
                                                _dev(R_parent, "reg"), s)
@@ -1132,9 +1157,9 @@ class AmrSolver:
         if l + 1 < self.nl:
             R = self.reg[l + 1]
             R.zero_()
-            self._advance(l + 1, 0.5 * dt, self.old[l], self.U[l], 0.0, R)
-            self._advance(l + 1, 0.5 * dt, self.old[l], self.U[l], 0.5, R)
-            child = self._lvl(l + 1)
+            self._advance(l + 1, 0.5 * dt, old, new, 0.0, R)
+            self._advance(l + 1, 0.5 * dt, old, new, 0.5, R)
+            child = self._lvl(l + 1)   # two substeps: back in its own tensor
             _check(lib.hydro_amr_restrict(ctypes.byref(child), ctypes.byref(fine), code, s), "hydro_amr_restrict")
             st = lib.hydro_amr_fixup(ctypes.byref(fine), ctypes.byref(child), _dev(self.flux[l], "flux"),
                                      _dev(R, "reg"), dt / dx, self._bcarr, code, s)
