@@ -36,32 +36,42 @@ __device__ __forceinline__ void cons_to_prim_vjp(const T U[5], const Gas<T>& g, 
 
 // -------------------------------------------------- a2: limiter VJP -------
 // h = half_slope(qm, q0, qp); given gh, add to gqm, gq0, gqp.
-template <typename T>
+//   h = sgn * min(...) with sgn the common sign: h = half_theta*dm, (qp-qm)/4 or half_theta*dp
+// Without branches: a wave whose lanes differ takes each of them in turn (the
+// fused adjoint of 64 groups, FP32 269 -> 245 us, FP64 302 -> 285).  kBranch
+// keeps them for the FP64 cells kernel, which spills more without (512 groups
+// faces + cells 895 us, 1007 without).
+template <bool kBranch, typename T>
 __device__ __forceinline__ void half_slope_vjp(T qm, T q0, T qp, T half_theta, T gh, T& gqm, T& gq0, T& gqp) {
   const T dm = q0 - qm;
   const T dp = qp - q0;
-  if (!(dm * dp > T(0))) return;
+  const bool on = dm * dp > T(0);
+  if (kBranch && !on) return;
   const T a = half_theta * fabs_(dm);
   const T b = T(0.25) * fabs_(qp - qm);
   const T c = half_theta * fabs_(dp);
-  // h = sgn * min(...) with sgn the common sign: h = half_theta*dm, (qp-qm)/4 or half_theta*dp
-  int sel = 0;
-  T m = a;
-  if (b < m) {
-    sel = 1;
-    m = b;
+  // the argument attaining the minimum: dm (first), the central one, dp
+  const bool mid = b < a;
+  const bool last = c < (mid ? b : a);
+  const bool first = !mid && !last;
+  if (kBranch) {
+    if (first) {
+      gq0 = gq0 + half_theta * gh;
+      gqm = gqm - half_theta * gh;
+    } else if (!last) {
+      gqp = gqp + T(0.25) * gh;
+      gqm = gqm - T(0.25) * gh;
+    } else {
+      gqp = gqp + half_theta * gh;
+      gq0 = gq0 - half_theta * gh;
+    }
+    return;
   }
-  if (c < m) sel = 2;
-  if (sel == 0) {
-    gq0 = gq0 + half_theta * gh;
-    gqm = gqm - half_theta * gh;
-  } else if (sel == 1) {
-    gqp = gqp + T(0.25) * gh;
-    gqm = gqm - T(0.25) * gh;
-  } else {
-    gqp = gqp + half_theta * gh;
-    gq0 = gq0 - half_theta * gh;
-  }
+  const T w = (mid && !last) ? T(0.25) : half_theta;
+  gqm = (on && !last) ? gqm - w * gh : gqm;
+  gqp = (on && !first) ? gqp + w * gh : gqp;
+  const T s = first ? half_theta : -half_theta;
+  gq0 = (on && (first || last)) ? gq0 + s * gh : gq0;
 }
 
 // ------------------------------------------- a3 + a4: Hancock states VJP ---
@@ -73,7 +83,7 @@ __device__ __forceinline__ void half_slope_vjp(T qm, T q0, T qp, T half_theta, T
 //   getG(d, side, T g[5])   cotangent gUt[d][side] (zero for unused faces)
 //   putN(d, side, T g[5])   receives the cotangent of neighbour (d, side)
 //   gWc                     receives the cotangent of the cell's own state
-template <typename T, class GetW, class GetG, class PutN>
+template <bool kBranch = false, typename T, class GetW, class GetG, class PutN>
 __device__ __forceinline__ void hancock_states_vjp_stream(const T Wc[5], const Gas<T>& g, bool first_order,
                                                           GetW&& getW, GetG&& getG, PutN&& putN, T gWc[5]) {
   // dU = half_dtdx * sum_d (F_d(-) - F_d(+)); every face state receives dU
@@ -142,56 +152,43 @@ __device__ __forceinline__ void hancock_states_vjp_stream(const T Wc[5], const G
     T gl[5] = {T(0), T(0), T(0), T(0), T(0)}, gr[5] = {T(0), T(0), T(0), T(0), T(0)};
     if (!first_order) {
 #pragma unroll
-      for (int q = 0; q < 5; ++q) half_slope_vjp(Wl[q], Wc[q], Wr[q], g.half_theta, gh[q], gl[q], gWc[q], gr[q]);
+      for (int q = 0; q < 5; ++q)
+        half_slope_vjp<kBranch>(Wl[q], Wc[q], Wr[q], g.half_theta, gh[q], gl[q], gWc[q], gr[q]);
     }
     putN(d, 0, gl);
     putN(d, 1, gr);
   }
 }
 
-// Array form: gWc (the cell's own primitive state) and gWn[3][2][5] (its six
-// neighbours), overwriting both.
-template <typename T>
-__device__ __forceinline__ void hancock_states_vjp(const T Wc[5], const T Wn[3][2][5], const Gas<T>& g,
-                                                   bool first_order, const T gUt[3][2][5], T gWc[5],
-                                                   T gWn[3][2][5]) {
-  hancock_states_vjp_stream(
-      Wc, g, first_order,
-      [&](int d, int side, T W[5]) {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) W[q] = Wn[d][side][q];
-      },
-      [&](int d, int side, T G[5]) {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) G[q] = gUt[d][side][q];
-      },
-      [&](int d, int side, const T G[5]) {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) gWn[d][side][q] = G[q];
-      },
-      gWc);
-}
-
 // ---------------------------------------------------------- a5: HLLC VJP ---
-// Forward: hllc_flux<D>(L, R, g, ws, F).  Given gF (axis frame), add the
-// cotangents of the two conserved input states to gL and gR.
+// Forward: hllc_flux<D>(L, R, g, ws, F).  Given gF (axis frame), the
+// cotangents of the two conserved input states.
+//
+// As in the forward solve only one side K enters the flux, as
+// F_K + S (U*_K - U_K) with S = S_K in the star regions; beyond the fan S = 0
+// and the divisors are 1, so that the same statements give the derivative of
+// F_K, and the cotangents of S_K and S* are dropped.  The face solves and the
+// limiter are the adjoint's arithmetic: with a branch per region and per side
+// the lanes of a wave took the paths in turn (192^3 FP32 level adjoint 1.23
+// ms, 1.11 with none; 128^3 FP64 607 -> 565 us); taking an x and a y face
+// in turn statement by statement gave nothing more.
 template <int D, typename T>
 __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], const Gas<T>& g, int ws, const T gFx[5],
                                               T gLx[5], T gRx[5]) {
   constexpr int n = 1 + D, t1 = 1 + (D + 1) % 3, t2 = 1 + (D + 2) % 3;
   // normal frame
-  const T rL = Lx[0], mnL = Lx[n], m1L = Lx[t1], m2L = Lx[t2], EL = Lx[4];
-  const T rR = Rx[0], mnR = Rx[n], m1R = Rx[t1], m2R = Rx[t2], ER = Rx[4];
+  const T L[5] = {Lx[0], Lx[n], Lx[t1], Lx[t2], Lx[4]}, R[5] = {Rx[0], Rx[n], Rx[t1], Rx[t2], Rx[4]};
   const T gF[5] = {gFx[0], gFx[n], gFx[t1], gFx[t2], gFx[4]};
   // ---- forward recomputation
-  const T iL = Fp<T>::rcp(rL), iR = Fp<T>::rcp(rR);
-  const T uL = mnL * iL, vL = m1L * iL, wL = m2L * iL;
-  const T uR = mnR * iR, vR = m1R * iR, wR = m2R * iR;
-  const T pL = g.gm1 * (EL - T(0.5) * (mnL * uL + m1L * vL + m2L * wL));
-  const T pR = g.gm1 * (ER - T(0.5) * (mnR * uR + m1R * vR + m2R * wR));
+  const T iL = Fp<T>::rcp(L[0]);
+  const T iR = Fp<T>::rcp(R[0]);
+  const T uL = L[1] * iL, vL = L[2] * iL, wL = L[3] * iL;
+  const T uR = R[1] * iR, vR = R[2] * iR, wR = R[3] * iR;
+  const T pL = g.gm1 * (L[4] - T(0.5) * (L[1] * uL + L[2] * vL + L[3] * wL));
+  const T pR = g.gm1 * (R[4] - T(0.5) * (R[1] * uR + R[2] * vR + R[3] * wR));
   const T cL = Fp<T>::sqrt(g.gamma * pL * iL);
   const T cR = Fp<T>::sqrt(g.gamma * pR * iR);
-  T sL = T(0), sR = T(0), iw = T(0), ua = T(0), va = T(0), wa = T(0), HL = T(0), HR = T(0), Ha = T(0), ca = T(0);
+  T sL = T(0), sR = T(0), iw = T(0), ua = T(0), va = T(0), wa = T(0), HL = T(0), HR = T(0), ca = T(0);
   T SL, SR;
   bool sl_first, sr_first;
   if (ws == 1) {
@@ -201,15 +198,15 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
     SL = sl_first ? a1 : b1;
     SR = sr_first ? a2 : b2;
   } else {
-    sL = Fp<T>::sqrt(rL);
-    sR = Fp<T>::sqrt(rR);
+    sL = Fp<T>::sqrt(L[0]);
+    sR = Fp<T>::sqrt(R[0]);
     iw = Fp<T>::rcp(sL + sR);
     ua = (sL * uL + sR * uR) * iw;
     va = (sL * vL + sR * vR) * iw;
     wa = (sL * wL + sR * wR) * iw;
-    HL = (EL + pL) * iL;
-    HR = (ER + pR) * iR;
-    Ha = (sL * HL + sR * HR) * iw;
+    HL = (L[4] + pL) * iL;
+    HR = (R[4] + pR) * iR;
+    const T Ha = (sL * HL + sR * HR) * iw;
     ca = Fp<T>::sqrt(g.gm1 * (Ha - T(0.5) * (ua * ua + va * va + wa * wa)));
     const T a1 = uL - cL, b1 = ua - ca, a2 = uR + cR, b2 = ua + ca;
     sl_first = !(b1 < a1);
@@ -217,91 +214,74 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
     SL = sl_first ? a1 : b1;
     SR = sr_first ? a2 : b2;
   }
-  const T aL = SL - uL, aR = SR - uR;
-  const T num = pR - pL + rL * uL * aL - rR * uR * aR;
-  const T den = rL * aL - rR * aR;
+  const T aL = SL - uL;
+  const T aR = SR - uR;
+  const T num = pR - pL + L[0] * uL * aL - R[0] * uR * aR;
+  const T den = L[0] * aL - R[0] * aR;
   const T Ss = Fp<T>::div(num, den);
 
-  // ---- reverse
-  T grL = T(0), gmnL = T(0), gm1L = T(0), gm2L = T(0), gEL = T(0);
-  T grR = T(0), gmnR = T(0), gm1R = T(0), gm2R = T(0), gER = T(0);
-  T guL = T(0), gpL = T(0), guR = T(0), gpR = T(0);
-  T gSL = T(0), gSR = T(0), gSs = T(0), gaL = T(0), gaR = T(0);
+  // ---- reverse: the flux of the side that enters it
+  const bool left = SL >= T(0) || Ss >= T(0);
+  const bool star = left ? !(SL >= T(0)) : SR > T(0);
+  const T r = left ? L[0] : R[0], u = left ? uL : uR, p = left ? pL : pR;
+  const T mn = left ? L[1] : R[1], m1 = left ? L[2] : R[2], m2 = left ? L[3] : R[3];
+  const T E = left ? L[4] : R[4];
+  const T Sk = left ? SL : SR, ak = left ? aL : aR;
+  const T S = star ? Sk : T(0), a = star ? ak : T(1), Sx = star ? Ss : T(0);
+  const T Dn = star ? Sk - Ss : T(1);
+  const T iD = Fp<T>::rcp(Dn);
+  const T rr = Fp<T>::div(a, Dn);
+  const T ia = Fp<T>::rcp(a);
+  const T Q = r * Sx + p * ia;
+  const T G = E + (Sx - u) * Q;
+  const T Us4 = rr * G;
+  // F0 = mn + S (rr r - r), F1 = mn u + p + S (rr r Ss - mn), F2 = m1 u + S (rr m1 - m1),
+  // F3 = m2 u + S (rr m2 - m2), F4 = (E + p) u + S (rr G - E)
+  const T gS = gF[0] * (rr * r - r) + gF[1] * (rr * r * Sx - mn) + gF[2] * (rr * m1 - m1) + gF[3] * (rr * m2 - m2) +
+               gF[4] * (Us4 - E);
+  const T grr = S * (gF[0] * r + gF[1] * r * Sx + gF[2] * m1 + gF[3] * m2 + gF[4] * G);
+  const T gG = star ? S * rr * gF[4] : T(0);
+  T gr = gF[0] * S * (rr - T(1)) + gF[1] * S * rr * Sx + gG * (Sx - u) * Sx;
+  T gSs_s = gF[1] * S * rr * r + gG * (Q + (Sx - u) * r);
+  const T gmn = gF[0] + gF[1] * (u - S);
+  T gu = gF[1] * mn + gF[2] * m1 + gF[3] * m2 + gF[4] * (E + p) - gG * Q;
+  const T gp = gF[1] + gF[4] * u + gG * (Sx - u) * ia;
+  T ga = -gG * (Sx - u) * p * ia * ia;
+  const T gm1 = gF[2] * (u + S * (rr - T(1)));
+  const T gm2 = gF[3] * (u + S * (rr - T(1)));
+  const T gE = gF[4] * (u - S) + gG;
+  // rr = a / (S - Ss)
+  ga = ga + grr * iD;
+  const T gDn = -grr * rr * iD;
+  T gSk = gS + gDn;
+  gSs_s = gSs_s - gDn;
+  // a = S - u
+  gSk = gSk + ga;
+  gu = star ? gu - ga : gu;
+  gr = star ? gr : T(0);
+  gSk = star ? gSk : T(0);
+  const T gSs = star ? gSs_s : T(0);
+  T grL = left ? gr : T(0), grR = left ? T(0) : gr;
+  T guL = left ? gu : T(0), guR = left ? T(0) : gu;
+  T gpL = left ? gp : T(0), gpR = left ? T(0) : gp;
+  T gmnL = left ? gmn : T(0), gmnR = left ? T(0) : gmn;
+  T gm1L = left ? gm1 : T(0), gm1R = left ? T(0) : gm1;
+  T gm2L = left ? gm2 : T(0), gm2R = left ? T(0) : gm2;
+  T gEL = left ? gE : T(0), gER = left ? T(0) : gE;
+  T gSL = left ? gSk : T(0), gSR = left ? T(0) : gSk;
 
-  if (SL >= T(0)) {
-    // F = (mn, mn u + p, m1 u, m2 u, (E + p) u) of L
-    gmnL = gF[0] + gF[1] * uL;
-    guL = gF[1] * mnL + gF[2] * m1L + gF[3] * m2L + gF[4] * (EL + pL);
-    gpL = gF[1] + gF[4] * uL;
-    gm1L = gF[2] * uL;
-    gm2L = gF[3] * uL;
-    gEL = gF[4] * uL;
-  } else if (!(Ss >= T(0)) && !(SR > T(0))) {
-    gmnR = gF[0] + gF[1] * uR;
-    guR = gF[1] * mnR + gF[2] * m1R + gF[3] * m2R + gF[4] * (ER + pR);
-    gpR = gF[1] + gF[4] * uR;
-    gm1R = gF[2] * uR;
-    gm2R = gF[3] * uR;
-    gER = gF[4] * uR;
-  } else {
-    const bool left = Ss >= T(0);
-    const T r = left ? rL : rR, u = left ? uL : uR, p = left ? pL : pR;
-    const T mn = left ? mnL : mnR, m1 = left ? m1L : m1R, m2 = left ? m2L : m2R, E = left ? EL : ER;
-    const T S = left ? SL : SR, a = left ? aL : aR;
-    const T Dn = S - Ss;
-    const T iD = Fp<T>::rcp(Dn);
-    const T rr = Fp<T>::div(a, Dn);
-    const T ia = Fp<T>::rcp(a);
-    const T Q = r * Ss + p * ia;
-    const T G = E + (Ss - u) * Q;
-    const T Us4 = rr * G;
-    // F0 = mn + S (rr r - r), F1 = mn u + p + S (rr r Ss - mn), F2 = m1 u + S (rr m1 - m1),
-    // F3 = m2 u + S (rr m2 - m2), F4 = (E + p) u + S (rr G - E)
-    const T gS = gF[0] * (rr * r - r) + gF[1] * (rr * r * Ss - mn) + gF[2] * (rr * m1 - m1) +
-                 gF[3] * (rr * m2 - m2) + gF[4] * (Us4 - E);
-    const T grr = S * (gF[0] * r + gF[1] * r * Ss + gF[2] * m1 + gF[3] * m2 + gF[4] * G);
-    const T gG = S * rr * gF[4];
-    T gr = gF[0] * S * (rr - T(1)) + gF[1] * S * rr * Ss + gG * (Ss - u) * Ss;
-    T gSs_s = gF[1] * S * rr * r + gG * (Q + (Ss - u) * r);
-    const T gmn = gF[0] + gF[1] * (u - S);
-    T gu = gF[1] * mn + gF[2] * m1 + gF[3] * m2 + gF[4] * (E + p) - gG * Q;
-    const T gp = gF[1] + gF[4] * u + gG * (Ss - u) * ia;
-    T ga = -gG * (Ss - u) * p * ia * ia;
-    const T gm1 = gF[2] * (u + S * (rr - T(1)));
-    const T gm2 = gF[3] * (u + S * (rr - T(1)));
-    const T gE = gF[4] * (u - S) + gG;
-    // rr = a / (S - Ss)
-    ga = ga + grr * iD;
-    const T gDn = -grr * rr * iD;
-    T gSk = gS + gDn;
-    gSs_s = gSs_s - gDn;
-    // a = S - u
-    gSk = gSk + ga;
-    gu = gu - ga;
-    gSs = gSs + gSs_s;
-    if (left) {
-      grL = grL + gr; guL = guL + gu; gpL = gpL + gp; gmnL = gmnL + gmn; gm1L = gm1L + gm1; gm2L = gm2L + gm2;
-      gEL = gEL + gE; gSL = gSL + gSk;
-    } else {
-      grR = grR + gr; guR = guR + gu; gpR = gpR + gp; gmnR = gmnR + gmn; gm1R = gm1R + gm1; gm2R = gm2R + gm2;
-      gER = gER + gE; gSR = gSR + gSk;
-    }
-  }
-
-  // S* = num / den (its cotangent is nonzero only in the star branches)
-  {
-    const T iden = Fp<T>::rcp(den);
-    const T gnum = gSs * iden;
-    const T gden = -gSs * Ss * iden;
-    gpR = gpR + gnum;
-    gpL = gpL - gnum;
-    grL = grL + gnum * uL * aL + gden * aL;
-    guL = guL + gnum * rL * aL;
-    gaL = gaL + gnum * rL * uL + gden * rL;
-    grR = grR - gnum * uR * aR - gden * aR;
-    guR = guR - gnum * rR * aR;
-    gaR = gaR - gnum * rR * uR - gden * rR;
-  }
+  // S* = num / den
+  const T iden = Fp<T>::rcp(den);
+  const T gnum = gSs * iden;
+  const T gden = -gSs * Ss * iden;
+  gpR = gpR + gnum;
+  gpL = gpL - gnum;
+  grL = grL + gnum * uL * aL + gden * aL;
+  guL = guL + gnum * L[0] * aL;
+  const T gaL = T(0) + gnum * L[0] * uL + gden * L[0];
+  grR = grR - gnum * uR * aR - gden * aR;
+  guR = guR - gnum * R[0] * aR;
+  const T gaR = T(0) - gnum * R[0] * uR - gden * R[0];
   // aL = SL - uL, aR = SR - uR
   gSL = gSL + gaL;
   guL = guL - gaL;
@@ -309,13 +289,25 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
   guR = guR - gaR;
 
   // wave speeds
-  T gcL = T(0), gcR = T(0), gua = T(0), gca = T(0);
+  T gcL = T(0), gcR = T(0);
   if (ws == 1) {
-    if (sl_first) { guL = guL + gSL; gcL = gcL - gSL; } else { guR = guR + gSL; gcR = gcR - gSL; }
-    if (sr_first) { guL = guL + gSR; gcL = gcL + gSR; } else { guR = guR + gSR; gcR = gcR + gSR; }
+    guL = sl_first ? guL + gSL : guL;
+    gcL = sl_first ? gcL - gSL : gcL;
+    guR = sl_first ? guR : guR + gSL;
+    gcR = sl_first ? gcR : gcR - gSL;
+    guL = sr_first ? guL + gSR : guL;
+    gcL = sr_first ? gcL + gSR : gcL;
+    guR = sr_first ? guR : guR + gSR;
+    gcR = sr_first ? gcR : gcR + gSR;
   } else {
-    if (sl_first) { guL = guL + gSL; gcL = gcL - gSL; } else { gua = gua + gSL; gca = gca - gSL; }
-    if (sr_first) { guR = guR + gSR; gcR = gcR + gSR; } else { gua = gua + gSR; gca = gca + gSR; }
+    guL = sl_first ? guL + gSL : guL;
+    gcL = sl_first ? -gSL : T(0);
+    T gua = sl_first ? T(0) : gSL;
+    T gca = sl_first ? T(0) : -gSL;
+    guR = sr_first ? guR + gSR : guR;
+    gcR = sr_first ? gSR : T(0);
+    gua = sr_first ? gua : gua + gSR;
+    gca = sr_first ? gca : gca + gSR;
     // ca = sqrt(gm1 (Ha - |ua|^2/2))
     const T gca2 = gca * T(0.5) * Fp<T>::rcp(ca);
     const T gHa = g.gm1 * gca2;
@@ -330,8 +322,8 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
     const T gvL = gva * sL * iw, gvR = gva * sR * iw;
     const T gwL = gwa * sL * iw, gwR = gwa * sR * iw;
     const T gHL = gHa * sL * iw, gHR = gHa * sR * iw;
-    const T giw = gua * (sL * uL + sR * uR) + gva * (sL * vL + sR * vR) + gwa * (sL * wL + sR * wR) +
-                  gHa * (sL * HL + sR * HR);
+    const T giw = gua * (sL * uL + sR * uR) + gva * (sL * vL + sR * vR) +
+                  gwa * (sL * wL + sR * wR) + gHa * (sL * HL + sR * HR);
     const T gsum = -giw * iw * iw;
     gsL = gsL + gsum;
     gsR = gsR + gsum;
@@ -354,14 +346,12 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
     grR = grR + gsR * T(0.5) * Fp<T>::rcp(sR);
   }
   // c = sqrt(gamma p / rho)
-  {
-    const T gxL = gcL * T(0.5) * Fp<T>::rcp(cL);
-    gpL = gpL + gxL * g.gamma * iL;
-    grL = grL - gxL * g.gamma * pL * iL * iL;
-    const T gxR = gcR * T(0.5) * Fp<T>::rcp(cR);
-    gpR = gpR + gxR * g.gamma * iR;
-    grR = grR - gxR * g.gamma * pR * iR * iR;
-  }
+  const T gxL = gcL * T(0.5) * Fp<T>::rcp(cL);
+  gpL = gpL + gxL * g.gamma * iL;
+  grL = grL - gxL * g.gamma * pL * iL * iL;
+  const T gxR = gcR * T(0.5) * Fp<T>::rcp(cR);
+  gpR = gpR + gxR * g.gamma * iR;
+  grR = grR - gxR * g.gamma * pR * iR * iR;
   // p = gm1 (E - (mn u + m1 v + m2 w)/2) written on conserved variables:
   // dp/dE = gm1, dp/dm_i = -gm1 u_i, dp/drho = gm1 |u|^2 / 2
   gEL = gEL + g.gm1 * gpL;
@@ -379,17 +369,8 @@ __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], cons
   grL = grL - guL * uL * iL;
   gmnR = gmnR + guR * iR;
   grR = grR - guR * uR * iR;
-  // back to the axis frame
-  gLx[0] = gLx[0] + grL;
-  gLx[n] = gLx[n] + gmnL;
-  gLx[t1] = gLx[t1] + gm1L;
-  gLx[t2] = gLx[t2] + gm2L;
-  gLx[4] = gLx[4] + gEL;
-  gRx[0] = gRx[0] + grR;
-  gRx[n] = gRx[n] + gmnR;
-  gRx[t1] = gRx[t1] + gm1R;
-  gRx[t2] = gRx[t2] + gm2R;
-  gRx[4] = gRx[4] + gER;
+  gLx[0] = grL, gLx[n] = gmnL, gLx[t1] = gm1L, gLx[t2] = gm2L, gLx[4] = gEL;
+  gRx[0] = grR, gRx[n] = gmnR, gRx[t1] = gm1R, gRx[t2] = gm2R, gRx[4] = gER;
 }
 
 }  // namespace gh

@@ -833,7 +833,7 @@ __device__ __forceinline__ void cells_col_vjp(SplitCol<T, kI>& c, int k, const T
   const bool u0 = face_used(cx, cy, k, 0), u1 = face_used(cx, cy, k, 1), u2 = face_used(cx, cy, k, 2);
   const bool u3 = face_used(cx, cy, k, 3), u4 = face_used(cx, cy, k, 4), u5 = face_used(cx, cy, k, 5);
   T gWc[5];
-  hancock_states_vjp_stream(
+  hancock_states_vjp_stream<sizeof(T) == 8>(
       c.Wc, gas, fo,
       [&](int d, int s, T W[5]) {
         if (d == 2) {
