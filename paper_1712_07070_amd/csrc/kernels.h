@@ -26,11 +26,18 @@ struct CflOut {
   double gamma;
 };
 
-// z segments per 16^3 group of a march over G groups whose workgroups fit
-// `slots` to a compute unit (256 of them).  A segment of n planes runs n + 2
-// iterations (it recomputes the states of one plane beyond each end); m
-// workgroups on a unit take 1 + share (m - 1) times as long as one (measured
-// per kernel).  The split with the least time on the fullest unit is taken,
+// Time of the fullest compute unit (256 of them) in a launch of `wgs` equal
+// workgroups of which `slots` fit to a unit, in times of one workgroup alone:
+// m of them together take 1 + share (m - 1) times as long (measured per
+// kernel).
+inline double fullest_unit(int64_t wgs, int slots, double share) {
+  const int64_t n = (wgs + 255) / 256, rest = n % slots;
+  return double(n / slots) * (1.0 + share * (slots - 1)) + (rest ? 1.0 + share * double(rest - 1) : 0.0);
+}
+
+// z segments per 16^3 group of a march over G groups.  A segment of n planes
+// runs n + 2 iterations (it recomputes the states of one plane beyond each
+// end).  The split with the least time on the fullest unit is taken,
 // the fewest segments on ties.  PPM step, FP64 (share 0.36), by 1, 2, 4, 8, 16
 // segments: 16 groups 169, 93, 55, 36, 29 us; 64 groups 173, 96, 61, 52, 75;
 // 192 groups 175, 121, 132, 145, 208; 512 groups 230, 249, 292, 375, 538.
@@ -38,9 +45,7 @@ inline int march_segments(int64_t G, int slots, double share) {
   int best = 1;
   double cost = 0.0;
   for (int s = 1; s <= 16; s *= 2) {
-    const int64_t n = (G * s + 255) / 256, rest = n % slots;
-    const double full = double(n / slots) * (1.0 + share * (slots - 1));
-    const double c = (full + (rest ? 1.0 + share * double(rest - 1) : 0.0)) * (16 / s + 2);
+    const double c = fullest_unit(G * s, slots, share) * (16 / s + 2);
     if (s == 1) cost = 0.9 * c;  // a split has to gain clearly
     else if (c < cost) {
       best = s;

@@ -163,6 +163,26 @@ __device__ __forceinline__ bool in_state_plane(int x, int y, int z) {
   return (hx || hy) && z >= 0 && z <= 15;
 }
 
+// Few groups leave the chip idle (one workgroup each, 256 compute units), and
+// their march takes as long as that of 256: see adj_segments.
+//
+// The planes [lo, hi) of the [-2, 17] box a workgroup writes: all of them, or
+// one z segment of a group that several workgroups share.  A segment runs the
+// iterations lo - 2 .. hi + 1 (within -1 .. 17): plane z takes the reverse
+// predictors of z - 1, z and z + 1 and is complete one iteration after the
+// last of them, and the reverse predictor of plane lo - 1 needs the z face
+// state of plane lo - 2.
+struct AdjAll {
+  static constexpr int lo = -2, hi = 18;
+};
+struct AdjPart {
+  int lo, hi;
+};
+template <class Z> __device__ __forceinline__ int adj_first(const Z& zr) { return zr.lo > 1 ? zr.lo - 2 : -1; }
+template <class Z> __device__ __forceinline__ int adj_last(const Z& zr) { return zr.hi < 16 ? zr.hi + 1 : 17; }
+// first plane whose predictor is reversed
+template <class Z> __device__ __forceinline__ int adj_rev(const Z& zr) { return zr.lo > 0 ? zr.lo - 1 : -1; }
+
 // Per-column state of one role (interior or halo column) across the march.
 // The column's primitive states of planes k-2, k-1, k are read back from the
 // LDS planes (the column publishes its own values there); only W(k+1) lives
@@ -184,9 +204,10 @@ struct AdjCol {
   T A0[5], A1[5], A2[5];      // input cotangents of the column at planes k-2, k-1, k
 };
 
-template <typename T, bool kI, class Src>
+template <typename T, bool kI, class Src, class Z>
 __device__ __forceinline__ void adj_col_init(AdjCol<T, kI>& c, const Src& src, int cx, int cy, const Gas<T>& gas,
-                                             SmemF<T>& sm) {
+                                             SmemF<T>& sm, const Z& zr) {
+  const int k0 = adj_first(zr);
   c.cx = cx;
   c.cy = cy;
   c.xface16 = !kI && cx == 16;
@@ -194,12 +215,12 @@ __device__ __forceinline__ void adj_col_init(AdjCol<T, kI>& c, const Src& src, i
   c.col = src.col(cx, cy);
   if (kI) {
     T W[5];
-    load_prim<kI>(src, c.col, -2, gas, W);
+    load_prim<kI>(src, c.col, k0 - 1, gas, W);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) sm.P[pslot(-2)][q][pidx(cx, cy)] = W[q];
+    for (int q = 0; q < 5; ++q) sm.P[pslot(k0 - 1)][q][pidx(cx, cy)] = W[q];
   }
-  load_prim<kI>(src, c.col, -1, gas, c.Wp);  // published as plane -1 by the first iteration
-  load_cons<kI>(src, c.col, 0, c.Un);
+  load_prim<kI>(src, c.col, k0, gas, c.Wp);  // published as plane k0 by the first iteration
+  load_cons<kI>(src, c.col, k0 + 1, c.Un);
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
     c.gRx[q] = c.gRy[q] = c.gRz[q] = T(0);
@@ -227,9 +248,9 @@ __device__ __forceinline__ void adj_col_publish(AdjCol<T, kI>& c, const Src& src
 // halo column's two parts run on different waves, each with its own AdjCol
 // of the column (the reverse part needs nothing the forward part keeps in
 // registers: its face cotangent comes through LDS).
-template <typename T, bool kI, bool kFwd = true, bool kRev = true>
+template <typename T, bool kI, bool kFwd = true, bool kRev = true, class Z>
 __device__ __forceinline__ void adj_col_states(AdjCol<T, kI>& c, int k, const T* __restrict__ go, const Gas<T>& gas,
-                                               bool fo, int ws, SmemF<T>& sm) {
+                                               bool fo, int ws, SmemF<T>& sm, const Z& zr) {
   const int cx = c.cx, cy = c.cy;
   const int sk = pslot(k), sj = pslot(k - 1), si = pslot(k - 2);
   T gLz[5] = {T(0), T(0), T(0), T(0), T(0)};   // cotangent of the z+ face state of plane k-1
@@ -263,7 +284,7 @@ __device__ __forceinline__ void adj_col_states(AdjCol<T, kI>& c, int k, const T*
       for (int q = 0; q < 5; ++q) sm.H[q][slot] = c.xface16 ? Ut[0][0][q] : Ut[1][0][q];
     }
     if (kI) {
-      if (k >= 0) {
+      if (k > adj_first(zr)) {
         T gF[5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) gF[q] = gas.dtdx * (gout(go, q, cx, cy, k) - gout(go, q, cx, cy, k - 1));
@@ -275,7 +296,7 @@ __device__ __forceinline__ void adj_col_states(AdjCol<T, kI>& c, int k, const T*
   }
 
   const int j = k - 1;
-  if (kRev && j >= -1 && in_state_plane(cx, cy, j)) {
+  if (kRev && j >= adj_rev(zr) && in_state_plane(cx, cy, j)) {
     const bool u0 = face_used(cx, cy, j, 0), u1 = face_used(cx, cy, j, 1), u2 = face_used(cx, cy, j, 2);
     const bool u3 = face_used(cx, cy, j, 3), u4 = face_used(cx, cy, j, 4), u5 = face_used(cx, cy, j, 5);
     T Wj[5], gWc[5];
@@ -333,10 +354,10 @@ __device__ __forceinline__ void adj_col_states(AdjCol<T, kI>& c, int k, const T*
 
 // F3a: the x and y face VJPs an interior column solves at plane k (its x-
 // face and y- face).
-template <typename T, bool kI>
+template <typename T, bool kI, class Z>
 __device__ __forceinline__ void adj_col_faces(AdjCol<T, kI>& c, int k, const T* __restrict__ go, const Gas<T>& gas,
-                                              int ws, SmemF<T>& sm) {
-  if (k < 0 || k > 15) return;
+                                              int ws, SmemF<T>& sm, const Z& zr) {
+  if (k < 0 || k > 15 || k < adj_rev(zr) || k > zr.hi) return;
   const int cx = c.cx, cy = c.cy;
   if (kI) {
     {
@@ -373,10 +394,10 @@ __device__ __forceinline__ void adj_col_faces(AdjCol<T, kI>& c, int k, const T* 
 // on the same values as the y-normal solver, and the results rotated back.
 // The high-side states come from the halo columns (H); the cotangent of the
 // low-side state goes to GL, that of the high-side state to GR.
-template <typename T>
+template <typename T, class Z>
 __device__ __forceinline__ void adj_last_faces(int lane, int k, const T* __restrict__ go, const Gas<T>& gas, int ws,
-                                               SmemF<T>& sm) {
-  if (k < 0 || k > 15 || lane >= 32) return;
+                                               SmemF<T>& sm, const Z& zr) {
+  if (k < 0 || k > 15 || k < adj_rev(zr) || k > zr.hi || lane >= 32) return;
   const bool yf = lane >= 16;
   const int i = lane & 15;
   const int hx = yf ? i : 16, hy = yf ? 16 : i;    // the halo cell on the high side
@@ -441,22 +462,23 @@ __device__ __forceinline__ void adj_gather_plane(int x, int y, int j, const Smem
 // plane k-1 has run).  A column whose planes another wave publishes calls this
 // right after its reverse part, before the barrier that lets the publisher
 // overwrite that plane's LDS slot with plane k+1.
-template <typename T, bool kI, class Sink>
+template <typename T, bool kI, class Sink, class Z>
 __device__ __forceinline__ void adj_col_finalize_prev(const AdjCol<T, kI>& c, int k, const T* __restrict__ go,
-                                                      const Gas<T>& gas, const SmemF<T>& sm, const Sink& sink) {
-  if (k - 2 >= c.zlo && k - 2 <= c.zhi) finalize_cell_lds(sm, c.cx, c.cy, k - 2, c.A0, go, gas, sink);
+                                                      const Gas<T>& gas, const SmemF<T>& sm, const Sink& sink,
+                                                      const Z& zr) {
+  if (k - 2 >= c.zlo && k - 2 >= zr.lo && k - 2 <= c.zhi) finalize_cell_lds(sm, c.cx, c.cy, k - 2, c.A0, go, gas, sink);
 }
 
 // F3b: in-plane gather of plane k-1 into the column; finalize the planes that
 // are complete (k-2 unless kPrevDone; after the last plane also k-1 and k);
 // advance the rings.
-template <typename T, bool kI, class Src, class Sink, bool kPrevDone = false>
+template <typename T, bool kI, class Src, class Sink, class Z, bool kPrevDone = false>
 __device__ __forceinline__ void adj_col_finish(AdjCol<T, kI>& c, const Src& src, int k, const T* __restrict__ go,
-                                               const Gas<T>& gas, const SmemF<T>& sm, const Sink& sink) {
+                                               const Gas<T>& gas, const SmemF<T>& sm, const Sink& sink, const Z& zr) {
   const int j = k - 1;
-  if (j >= c.zlo && j <= c.zhi) adj_gather_plane(c.cx, c.cy, j, sm, c.A1);
-  if (!kPrevDone) adj_col_finalize_prev(c, k, go, gas, sm, sink);
-  if (k == 17) {
+  if (j >= c.zlo && j <= c.zhi && j >= zr.lo && j < zr.hi) adj_gather_plane(c.cx, c.cy, j, sm, c.A1);
+  if (!kPrevDone) adj_col_finalize_prev(c, k, go, gas, sm, sink, zr);
+  if (k == 17 && zr.hi == 18) {
     if (16 <= c.zhi) finalize_cell_lds(sm, c.cx, c.cy, 16, c.A1, go, gas, sink);
     if (17 <= c.zhi) finalize_cell_lds(sm, c.cx, c.cy, 17, c.A2, go, gas, sink);
   }
@@ -468,9 +490,10 @@ __device__ __forceinline__ void adj_col_finish(AdjCol<T, kI>& c, const Src& src,
   }
 }
 
-template <typename T, class Src, class Sink>
+template <typename T, class Src, class Sink, class Z = AdjAll>
 __device__ __forceinline__ void adjoint_fused(const Src& src, const T* __restrict__ go, const Gas<T>& gas,
-                                              int first_order, int ws, SmemF<T>& sm, const Sink& sink) {
+                                              int first_order, int ws, SmemF<T>& sm, const Sink& sink,
+                                              const Z zr = Z()) {
   const int tid = threadIdx.x;
   const bool halo = tid < 64;                  // wave 0: halo columns, forward part
   const bool hrev = (tid >> 6) == 1;           // wave 1: halo columns, reverse part and finish
@@ -501,17 +524,18 @@ __device__ __forceinline__ void adjoint_fused(const Src& src, const T* __restric
   // lanes without an edge column re-read their 2-deep column (unconditional loads)
   const int64_t col_edge = halo ? src.col(has_edge ? ex : ox, has_edge ? ey : oy) : 0;
 
+  const int kb = adj_first(zr), ke = adj_last(zr);
   AdjCol<T, true> ci;
   AdjCol<T, false> ch;  // wave 0: forward part; wave 1: reverse part of the same halo column
-  adj_col_init(ci, src, tid & 15, tid >> 4, gas, sm);
+  adj_col_init(ci, src, tid & 15, tid >> 4, gas, sm, zr);
   T Uo[5], Ue[5];  // halo role: 2-deep and edge column, plane k (in flight)
-  if (halo || hrev) adj_col_init(ch, src, hx, hy, gas, sm);
+  if (halo || hrev) adj_col_init(ch, src, hx, hy, gas, sm, zr);
   if (halo) {
-    load_cons<false>(src, col_out, 0, Uo);
-    load_cons<false>(src, col_edge, 0, Ue);
+    load_cons<false>(src, col_out, kb > 0 ? kb : 0, Uo);
+    load_cons<false>(src, col_edge, kb > 0 ? kb : 0, Ue);
   }
 
-  for (int k = -1; k <= 17; ++k) {
+  for (int k = kb; k <= ke; ++k) {
     const int sk = pslot(k);
     adj_col_publish(ci, src, k, gas, sm);
     if (k <= 16) {
@@ -535,21 +559,21 @@ __device__ __forceinline__ void adjoint_fused(const Src& src, const T* __restric
       }
     }
     __syncthreads();
-    adj_col_states(ci, k, go, gas, fo, ws, sm);
-    if (halo) adj_col_states<T, false, true, false>(ch, k, go, gas, fo, ws, sm);
+    adj_col_states(ci, k, go, gas, fo, ws, sm, zr);
+    if (halo && k >= adj_rev(zr) && k <= zr.hi) adj_col_states<T, false, true, false>(ch, k, go, gas, fo, ws, sm, zr);
     if (hrev) {
-      adj_col_states<T, false, false, true>(ch, k, go, gas, fo, ws, sm);
+      adj_col_states<T, false, false, true>(ch, k, go, gas, fo, ws, sm, zr);
       // wave 0 publishes this column: plane k-2's slot is rewritten after the barrier
-      adj_col_finalize_prev(ch, k, go, gas, sm, sink);
+      adj_col_finalize_prev(ch, k, go, gas, sm, sink, zr);
     }
     __syncthreads();
-    adj_col_faces(ci, k, go, gas, ws, sm);
-    if (last) adj_last_faces(tid & 63, k, go, gas, ws, sm);
-    adj_col_finish(ci, src, k, go, gas, sm, sink);
-    if (hrev) adj_col_finish<T, false, Src, Sink, true>(ch, src, k, go, gas, sm, sink);
+    adj_col_faces(ci, k, go, gas, ws, sm, zr);
+    if (last) adj_last_faces(tid & 63, k, go, gas, ws, sm, zr);
+    adj_col_finish(ci, src, k, go, gas, sm, sink, zr);
+    if (hrev) adj_col_finish<T, false, Src, Sink, Z, true>(ch, src, k, go, gas, sm, sink, zr);
     if (outer) {
       const int j = k - 1;
-      if (j >= 0 && j <= 15) {
+      if (j >= 0 && j <= 15 && j >= zr.lo && j < zr.hi) {
         // the 2-deep and edge columns get only in-plane contributions
         T g[5] = {T(0), T(0), T(0), T(0), T(0)};
         adj_gather_plane(fox, foy, j, sm, g);
@@ -1008,6 +1032,41 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(Adj
     adjoint_fused<T>(src, gout_ + g * 5 * 4096, gas, first_order, ws, sm, sink);
 }
 
+// Planes of segment i of n (2 <= n <= 14): the end segments start (end) at the
+// group's own end of the march, three iterations closer to their planes than
+// a middle one, and get three planes more.
+__device__ __forceinline__ AdjPart adj_part(int i, int n) {
+  return {i == 0 ? -2 : 1 + 14 * i / n, i == n - 1 ? 18 : 1 + 14 * (i + 1) / n};
+}
+
+// The fused kernels with every group's planes shared by `segs` workgroups.
+template <typename T>
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(AdjWaves<T>::value, AdjWaves<T>::value))) void adj_seg_padded(
+    const T* __restrict__ Upad, const T* __restrict__ gout_, T* __restrict__ gpad, int gh, Gas<T> gas, int first_order,
+    int ws, int segs) {
+  __shared__ SmemF<T> sm;
+  const int P = 16 + 2 * gh;
+  const int64_t g = blockIdx.x / unsigned(segs);
+  const int64_t P3 = int64_t(P) * P * P;
+  PaddedSource<T> src{Upad + g * 5 * P3, P, gh};
+  PadSink<T> sink{gpad + g * 5 * P3, P, gh};
+  adjoint_fused<T>(src, gout_ + g * 5 * 4096, gas, first_order, ws, sm, sink,
+                   adj_part(int(blockIdx.x % unsigned(segs)), segs));
+}
+
+template <typename T>
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(AdjWaves<T>::value, AdjWaves<T>::value))) void adj_seg_level(
+    const T* __restrict__ level, const T* __restrict__ gout_, T* __restrict__ gbox, LevelGeom geo, Gas<T> gas,
+    const double* __restrict__ dt_dev, double dx, int first_order, int ws, int segs) {
+  __shared__ SmemF<T> sm;
+  set_dt_adj(gas, dt_dev, dx);
+  const int64_t g = blockIdx.x / unsigned(segs);
+  LevelSource<T> src{level, geo, int(g % geo.ngx), int((g / geo.ngx) % geo.ngy), int(g / (int64_t(geo.ngx) * geo.ngy))};
+  BoxSink<T> sink{gbox + g * 5 * int64_t(kBox * kBox * kBox)};
+  adjoint_fused<T>(src, gout_ + g * 5 * 4096, gas, first_order, ws, sm, sink,
+                   adj_part(int(blockIdx.x % unsigned(segs)), segs));
+}
+
 template <typename T>
 __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void adj_faces_padded(
     const T* __restrict__ Upad, const T* __restrict__ gout_, T* __restrict__ ws, int gh, Gas<T> gas,
@@ -1247,6 +1306,31 @@ __global__ __launch_bounds__(256) void zero_kernel(T* __restrict__ p, int64_t n)
     p[i] = T(0);
 }
 
+// z segments per group of the fused adjoint.  A middle segment of n planes
+// runs n + 4 iterations and the longest one of s segments ceil(14 / s) + 5; the
+// whole march runs 19.  FP64 one workgroup to a compute unit, FP32 two.  Level
+// adjoint with its gather by 1, 2, 3, 4, 5, 7, 14 segments, us: FP64 8 groups
+// 282, 185, 151, 134, 117, 100, 82; 64 groups 291, 193, 158, 141, 214, 190, 261;
+// 192 groups 302, 377, 414, ...; 384 groups 597, 580, 706.  FP32 8 groups 244,
+// 158, 129, 114, 100, 86, 71; 96 groups 252, 165, 140, 126, 112, 157, 181; 256
+// groups 266, 186, 258, 247; 512 groups 301, 359.
+template <typename T>
+int adj_segments(int64_t G) {
+  const int slots = sizeof(T) == 8 ? 1 : 2;
+  const double share = 0.12;
+  const int splits[] = {2, 3, 4, 5, 7, 14};
+  int best = 1;
+  double cost = 0.9 * fullest_unit(G, slots, share) * 19;  // a split has to gain clearly
+  for (const int s : splits) {
+    const double c = fullest_unit(G * s, slots, share) * ((14 + s - 1) / s + 5);
+    if (c < cost) {
+      best = s;
+      cost = c;
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 size_t adjoint_workspace_elems(int64_t n_groups, bool level) {
@@ -1270,6 +1354,9 @@ hipError_t launch_mhm_adjoint_padded(const T* U_pad, const T* g_out, T* g_pad, i
                        ghost, gas, first_order, ws);
     hipLaunchKernelGGL(adj_cells_padded<T>, dim3(unsigned(G)), dim3(kAdjThreads), 0, stream, U_pad, g_out, work,
                        g_pad, ghost, gas, first_order);
+  } else if (const int segs = adj_segments<T>(G); segs > 1) {
+    hipLaunchKernelGGL(adj_seg_padded<T>, dim3(unsigned(G * segs)), dim3(kAdjThreads), 0, stream, U_pad, g_out, g_pad,
+                       ghost, gas, first_order, ws, segs);
   } else {
     hipLaunchKernelGGL(adj_fused_padded<T>, dim3(unsigned(G)), dim3(kAdjThreads), 0, stream, U_pad, g_out, g_pad,
                        ghost, gas, first_order, ws);
@@ -1293,6 +1380,9 @@ hipError_t launch_mhm_adjoint_level(const T* level, const T* g_out, T* g_in, con
                        gas, dt_dev, dx, first_order, ws);
     hipLaunchKernelGGL(adj_cells_level<T>, dim3(blocks), dim3(kAdjThreads), 0, stream, level, g_out, fws, gbox,
                        geo, gas, dt_dev, dx, first_order);
+  } else if (const int segs = adj_segments<T>(G); segs > 1) {
+    hipLaunchKernelGGL(adj_seg_level<T>, dim3(unsigned(G * segs)), dim3(kAdjThreads), 0, stream, level, g_out, gbox,
+                       geo, gas, dt_dev, dx, first_order, ws, segs);
   } else {
     hipLaunchKernelGGL(adj_fused_level<T>, dim3(blocks), dim3(kAdjThreads), 0, stream, level, g_out, gbox, geo,
                        gas, dt_dev, dx, first_order, ws);
