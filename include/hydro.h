@@ -333,14 +333,17 @@ int hydro_amr_fill_ghosts(const hydro_amr_level_t* fine, const hydro_amr_level_t
  *   U_out_dev      [G][5][16^3] new states; must not overlap the old ones
  *   U_pad_dev      scratch [G][5][P^3]: only ghost cells that no sibling holds
  *                  are written and read
- *   face_flux_dev  [G][9][5][16][16], written as by hydro_advance_ext for every
- *                  group with face_flux_all != 0, else for the groups with a
- *                  side that no sibling shares (what the flux registers read)
+ *   finer          the next finer level, or NULL if there is none
+ *   face_flux_dev  [G][9][5][16][16], layout of hydro_advance_ext: the planes
+ *                  that hydro_amr_flux_accumulate and hydro_amr_fixup read are
+ *                  written, those of a side that no sibling shares and those
+ *                  with a patch of `finer` on one side only
  *   Asynchronous on stream. */
 int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, const void* coarse_old_dev,
                       const void* coarse_new_dev, double a, const int32_t* bc_host, int32_t ghost, int32_t dtype,
                       double dt, double dx, double gamma, int32_t scheme, double theta, void* U_out_dev,
-                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, int32_t face_flux_all, void* stream);
+                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, const hydro_amr_level_t* finer,
+                      void* stream);
 int hydro_amr_flux_accumulate(const hydro_amr_level_t* fine, const void* face_flux_dev, double weight,
                               const int32_t* bc_host, int32_t dtype, void* reg_dev, void* stream);
 int hydro_amr_restrict(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, int32_t dtype, void* stream);

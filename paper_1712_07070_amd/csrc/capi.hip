@@ -838,7 +838,7 @@ int hydro_amr_fill_ghosts(const hydro_amr_level_t* fine, const hydro_amr_level_t
 int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* coarse, const void* coarse_old_dev,
                       const void* coarse_new_dev, double a, const int32_t* bc_host, int32_t ghost, int32_t dtype,
                       double dt, double dx, double gamma, int32_t scheme, double theta, void* U_out_dev,
-                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, int32_t face_flux_all, void* stream) {
+                      void* U_pad_dev, int32_t* n_bad_dev, void* face_flux_dev, const hydro_amr_level_t* finer, void* stream) {
   if (!amr_level_ok(fine, true) || !bc_ok(bc_host) || ghost < 2 || ghost > 16 || U_pad_dev == nullptr ||
       U_out_dev == nullptr || face_flux_dev == nullptr || (dtype != HYDRO_F64 && dtype != HYDRO_F32))
     return HYDRO_EINVAL;
@@ -852,6 +852,11 @@ int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* co
     C = amr_args(coarse);
   } else if (fine->n_groups != int64_t(fine->n[0]) * fine->n[1] * fine->n[2]) {
     return HYDRO_EINVAL;  // only a level covering the domain needs no coarse level
+  }
+  gh::AmrLevelArgs N{};
+  if (finer != nullptr) {
+    if (!amr_level_ok(finer, false) || !amr_pair_ok(finer, fine)) return HYDRO_EINVAL;
+    N = amr_args(finer);
   }
   const int64_t P = 16 + 2 * ghost, G = fine->n_groups;
   const size_t es = dtype_size(dtype), ub = size_t(G) * 5 * 4096 * es, pb = size_t(G) * 5 * P * P * P * es,
@@ -872,7 +877,7 @@ int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* co
     }
     return gh::launch_mhm_amr(static_cast<const T*>(fine->U_dev), static_cast<T*>(U_out_dev), amr_args(fine),
                               static_cast<const T*>(U_pad_dev), ghost, bc_host, make_gas<T>(gamma, theta, dt, dx),
-                              first_order, ws, n_bad_dev, static_cast<T*>(face_flux_dev), int(face_flux_all), s);
+                              first_order, ws, n_bad_dev, static_cast<T*>(face_flux_dev), N, s);
   };
   return device_status(dtype == HYDRO_F64 ? go(0.0) : go(0.0f));
 }

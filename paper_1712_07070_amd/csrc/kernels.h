@@ -245,11 +245,13 @@ __device__ __forceinline__ unsigned amr_outflow_faces(const AmrLevelArgs& F, con
 template <typename T>
 hipError_t launch_amr_fill_open(const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C, double a,
                                 const int bc[6], int ghost, T* pad, hipStream_t stream);
-// The default step of a level from its states and those blocks (mhm_amr.hip).
+// The default step of a level from its states and those blocks (mhm_amr.hip),
+// with the face fluxes that flux registers read (N: the next finer level, its map
+// null if there is none).
 template <typename T>
 hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* pad, int ghost, const int bc[6],
-                          const Gas<T>& gas, int first_order, int ws, int* n_bad, T* face_flux, int ff_all,
-                          hipStream_t stream);
+                          const Gas<T>& gas, int first_order, int ws, int* n_bad, T* face_flux,
+                          const AmrLevelArgs& N, hipStream_t stream);
 template <typename T>
 hipError_t launch_amr_fill(const T* Uf, const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C,
                            double a, const int bc[6], int ghost, T* pad, hipStream_t stream);

@@ -337,7 +337,7 @@ __device__ __forceinline__ int cfl_slot(int tid) {
 template <typename T, bool kI, class Src, int kL, class Sch, class Z>
 __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, typename Src::Off>& c, const Src& src, T* __restrict__ out, int k,
                                               const Gas<T>& gas, int first_order, int ws, Smem<T, kL>& sm, double* smax,
-                                              double gamma_d, T* __restrict__ ff, unsigned* rec, const Z& zr) {
+                                              double gamma_d, T* __restrict__ ff, unsigned* rec, const Z& zr, unsigned ff_planes) {
   const int cx = c.cx, cy = c.cy;
   int bad = 0;
   // U^n of plane k-1 for its update at the end of this phase, issued first
@@ -389,7 +389,7 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
       bool own = true;
       if constexpr (!std::is_same<Z, ZAll>::value) own = k < zr.hi || zr.hi == 16;
       bad += own ? bz : 0;
-      if (ff != nullptr && (k & 7) == 0 && own) {
+      if (ff != nullptr && (k & 7) == 0 && own && ((ff_planes >> (6 + (k >> 3))) & 1u)) {
         // z faces on a patch boundary (z = 0, 8, 16): plane 6 + k/8, entry y*16 + x
         T* o = ff + (6 + (k >> 3)) * 5 * 256 + cy * 16 + cx;
 #pragma unroll
@@ -456,12 +456,15 @@ __device__ __forceinline__ int fwd_col_faces(const Sch& sch, FwdCol<T, kI, Off>&
 constexpr int kFluxStage = 8 * 240;
 template <typename T, int kL>
 __device__ __forceinline__ void put_face_fluxes(int axis, int lane, int k, bool last, int first, const Smem<T, kL>& sm,
-                                                T* __restrict__ ff, T* stage) {
+                                                T* __restrict__ ff, T* stage, unsigned planes) {
+  planes >>= 3 * axis;
+  if ((planes & 7u) == 0) return;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int v = j * 64 + lane, pq = v >> 4, i = v & 15;  // pq = 5 (coordinate / 8) + field
     if (v >= 240) break;
     const int p = pq / 5, q = pq - 5 * p;
+    if (!((planes >> p) & 1u)) continue;
     if (axis == 0) ff[pq * 256 + k * 16 + i] = sm.F[0][q][fxidx(8 * p, i)];
     else stage[(k & 7) * 240 + v] = sm.F[1][q][fyidx(i, 8 * p)];
   }
@@ -469,6 +472,7 @@ __device__ __forceinline__ void put_face_fluxes(int axis, int lane, int k, bool 
     // planes k0 .. k of each row (the same lane stored them)
     const int k0 = (k & 8) > first ? (k & 8) : first;
     for (int v = lane; v < 240; v += 64) {
+      if (!((planes >> ((v >> 4) / 5)) & 1u)) continue;
       T* o = ff + (15 + (v >> 4)) * 256 + (v & 15) * 16;
       for (int z = k0; z <= k; ++z) o[z] = stage[(z & 7) * 240 + v];
     }
@@ -532,7 +536,7 @@ enum WaveRole { kRoleHalo = 0, kRoleLastFaces = 1, kRolePlain = 2 };
 template <typename T, class Src, int kRole, int kUnroll, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas, int first_order,
                                            int ws, Smem<T, kL>& sm, double* smax, double gamma_d, int tid,
-                                           T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage) {
+                                           T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage, unsigned ff_planes) {
   // halo role: side 0..3 = x-, x+, y-, y+; the column two cells out; lanes
   // 0..3 also one of the 4 edge columns
   const int lane = tid & 63;
@@ -586,9 +590,9 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 
     // ---- half-step face states of plane k; z-face and update of plane k-1
     if (kRole == kRolePlain && ff != nullptr && k > zr.lo)
-      put_face_fluxes(tid >> 7, lane, k - 1, k == zr.hi, zr.lo, sm, ff, ff_stage);
-    bad += fwd_col_states(sch, ci, src, out, k, gas, first_order, ws, sm, smax, gamma_d, ff, rec, zr);
-    if (kHalo) bad += fwd_col_states(sch, ch, src, out, k, gas, first_order, ws, sm, nullptr, gamma_d, (T*)nullptr, rec, zr);
+      put_face_fluxes(tid >> 7, lane, k - 1, k == zr.hi, zr.lo, sm, ff, ff_stage, ff_planes);
+    bad += fwd_col_states(sch, ci, src, out, k, gas, first_order, ws, sm, smax, gamma_d, ff, rec, zr, ff_planes);
+    if (kHalo) bad += fwd_col_states(sch, ch, src, out, k, gas, first_order, ws, sm, nullptr, gamma_d, (T*)nullptr, rec, zr, ff_planes);
     __syncthreads();
 
     // ---- x and y faces of plane k
@@ -610,7 +614,7 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 // each axis) to ff as [9][5][256]: plane 3 axis + k holds the faces at 8 k,
 // entry b * 16 + a with (a, b) the transverse coordinates in cyclic order
 // (the flux registers of coarse-fine coupling); ff_stage: kFluxStage elements of
-// LDS for it.  `tid` is the thread's index in the
+// LDS for it; ff_planes: bit 3 axis + k set for the planes to write.  `tid` is the thread's index in the
 // workgroup (a loop over groups passes it opaque, so that the compiler keeps
 // thread-derived addresses out of the loop's live set).  Wave 0 runs the
 // march with the halo roles, wave 2 with the last faces, waves 1 and 3 with
@@ -628,7 +632,8 @@ __device__ __forceinline__ int march_group(const Sch& sch, const Src& src, T* __
 template <typename T, bool kPrio, class Src, int kL, class Sch, class Z>
 __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __restrict__ out, const Gas<T>& gas,
                                            int first_order, int ws, Smem<T, kL>& sm, double* smax, double gamma_d,
-                                           int tid, T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage) {
+                                           int tid, T* __restrict__ ff, unsigned* rec, const Z& zr, T* ff_stage,
+                                           unsigned ff_planes) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Two planes per loop iteration, so that the register rotation of a
   // column's planes (Wm <- Wc <- Wp, z-face state and flux) becomes renaming
@@ -646,29 +651,29 @@ __device__ __forceinline__ int march_roles(const Sch& sch, const Src& src, T* __
   }
   if constexpr (std::is_same<Z, ZPart>::value) {
     // a z segment: few planes, one per loop iteration, one copy
-    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
-    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
   } else if constexpr (!std::is_same<Sch, DefaultScheme>::value) {
     // the other words: one copy (their options are run-time anyway), one
     // plane per loop iteration
-    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+    if (wave == 0) return march_group<T, Src, kRoleHalo, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
-    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      return march_group<T, Src, kRoleLastFaces, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
+    return march_group<T, Src, kRolePlain, 1>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
   } else {
     if (first_order == 0) {
-      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      if (wave == 0) return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
       if (wave == 2)
-        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
-      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+        return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
+      return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, 0, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
     }
     if (wave == 0)
-      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      return march_group<T, Src, kRoleHalo, kU>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
     if (wave == 2)
-      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
-    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage);
+      return march_group<T, Src, kRoleLastFaces, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
+    return march_group<T, Src, kRolePlain, kU2>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, rec, zr, ff_stage, ff_planes);
   }
 }
 
@@ -680,13 +685,13 @@ __device__ __forceinline__ int process_group(const Src& src, T* __restrict__ out
                                              int first_order, int ws, Smem<T, kL>& sm, double* smax,
                                              double gamma_d, int tid = threadIdx.x, T* __restrict__ ff = nullptr,
                                              unsigned* __restrict__ rec_out = nullptr, const Sch& sch = Sch(),
-                                             const Z& zr = Z(), T* ff_stage = nullptr) {
+                                             const Z& zr = Z(), T* ff_stage = nullptr, unsigned ff_planes = 0x1ffu) {
   if (rec_out == nullptr)
-    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr, zr, ff_stage);
+    return march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, nullptr, zr, ff_stage, ff_planes);
   __shared__ unsigned grp_rec;
   if (tid == 0) grp_rec = 0u;  // the march's first barrier orders this before any XOR
   unsigned h = 2166136261u ^ (unsigned(tid) * 0x9E3779B9u);
-  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h, zr, ff_stage);
+  const int bad = march_roles<T, kPrio>(sch, src, out, gas, first_order, ws, sm, smax, gamma_d, tid, ff, &h, zr, ff_stage, ff_planes);
   atomicXor(&grp_rec, h);
   __syncthreads();
   if (tid == 0) *rec_out = grp_rec;

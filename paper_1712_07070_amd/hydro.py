@@ -92,7 +92,7 @@ def load():
         "hydro_advance_level_fallback": (i32, [P, P, P, i32, i32, i32, P, i32, f64, f64, f64, f64, f64, i32, f64,
                                                P, i64, P, P]),
         "hydro_amr_fill_ghosts": (i32, [P, P, P, P, f64, P, i32, i32, P, P]),
-        "hydro_amr_advance": (i32, [P, P, P, P, f64, P, i32, i32, f64, f64, f64, i32, f64, P, P, P, P, i32, P]),
+        "hydro_amr_advance": (i32, [P, P, P, P, f64, P, i32, i32, f64, f64, f64, i32, f64, P, P, P, P, P, P]),
         "hydro_amr_flux_accumulate": (i32, [P, P, f64, P, i32, P, P]),
         "hydro_amr_restrict": (i32, [P, P, i32, P]),
         "hydro_amr_fixup": (i32, [P, P, P, P, f64, P, i32, P]),
@@ -1134,10 +1134,11 @@ class AmrSolver:
                 old, new = (self.U[l], self.alt[l]) if self.cur[l] == 0 else (self.alt[l], self.U[l])
                 self.cur[l] ^= 1
             src = self._lvl(l, old)
+            nxt = ctypes.byref(self._lvl(l + 1)) if l + 1 < self.nl else None
             st = lib.hydro_amr_advance(ctypes.byref(src), cptr, oldp, newp, float(a), self._bcarr, self.ghost, code,
                                        float(dt), float(dx), self.gamma, self.scheme, self.theta, _dev(new, "new"),
                                        _dev(self.pad[l], "pad"), _dev(self.n_bad, "n_bad"),
-                                       _dev(self.flux[l], "flux"), int(l + 1 < self.nl), s)
+                                       _dev(self.flux[l], "flux"), nxt, s)
             _check(st, "hydro_amr_advance")
         else:
             old, new = self.alt[l], self.U[l]

@@ -27,6 +27,45 @@ def boxes(n0, box):
     return pos
 
 
+def flux_planes(n0, pos, l, bc, coupled):
+    """[G, 9] bool: the planes of level l's groups read by hydro_amr_flux_accumulate
+    (open sides) and, when coupled to the next level, by hydro_amr_fixup (a face
+    between a refined patch and one that is not)."""
+    def level(m):
+        have = set(map(tuple, np.asarray(pos[m]).tolist()))
+        n = [v << m for v in n0]
+
+        def at(p):
+            p = list(p)
+            for d in range(3):
+                if p[d] < 0 or p[d] >= n[d]:
+                    if bc[2 * d + (p[d] >= n[d])] != 0:
+                        return None   # beyond an outflow face
+                    p[d] %= n[d]
+            return tuple(p) in have
+        return at
+    own, fine = level(l), level(l + 1) if coupled else None
+    need = np.zeros((len(pos[l]), 9), bool)
+    for g, p in enumerate(np.asarray(pos[l]).tolist()):
+        for d in range(3):
+            for k in range(3):
+                if k != 1:
+                    q = list(p)
+                    q[d] += k - 1
+                    need[g, 3 * d + k] |= own(q) is False
+                for a in range(2):
+                    for b in range(2):
+                        c = [2 * v for v in p]
+                        c[d] += k
+                        c[(d + 1) % 3] += a
+                        c[(d + 2) % 3] += b
+                        below = list(c)
+                        below[d] -= 1
+                        if coupled:
+                            need[g, 3 * d + k] |= bool(fine(below)) != bool(fine(c))
+    return need
+
+
 CASES = {
     # (level-0 lattice, box of refined patches (x, y, z), domain faces)
     "one group": ((2, 2, 2), ((1, 2), (1, 2), (1, 2)), (0,) * 6),
@@ -68,32 +107,23 @@ def test_amr_advance_equals_fill_and_step(hydro, dtype, case, ghost):
         pad = torch.zeros((G, 5, P, P, P), dtype=dtype, device="cuda")
         ff = torch.zeros((G, 9, 5, 16, 16), dtype=dtype, device="cuda")
         n_bad = torch.zeros(2, dtype=torch.int32, device="cuda")
+        count = 0
         assert lib.hydro_amr_fill_ghosts(ctypes.byref(fine), cp, old, new, a, s._bcarr, ghost, code, pad.data_ptr(),
                                          stream) == 0
         ref = hydro.advance_ext(pad, 1e-3, s.dx0 / 2 ** l, 5.0 / 3.0, 1, n_bad=n_bad[:1], face_flux=ff)
-        for every in (1, 0):
+        for finer in ((None, s._lvl(1)) if l == 0 else (None,)):
             out = torch.zeros_like(ref)
             scratch = torch.full_like(pad, float("nan"))   # what is read of it must have been written
             got = torch.zeros_like(ff)
             assert lib.hydro_amr_advance(ctypes.byref(fine), cp, old, new, a, s._bcarr, ghost, code, 1e-3,
                                          s.dx0 / 2 ** l, 5.0 / 3.0, 1, 1.5, out.data_ptr(), scratch.data_ptr(),
-                                         n_bad[1:].data_ptr(), got.data_ptr(), every, stream) == 0
+                                         n_bad[1:].data_ptr(), got.data_ptr(),
+                                         None if finer is None else ctypes.byref(finer), stream) == 0
             assert torch.equal(out, ref)
-            if every:
-                assert torch.equal(got, ff)
-            else:   # groups with an open side write theirs, the others nothing
-                wrote = (got != 0).flatten(1).any(1)
-                assert torch.equal(got[wrote], ff[wrote])
-                m = s.maps[l].cpu().numpy()
-                n = [v << l for v in n0]
-                for i, p in enumerate(pos[l]):
-                    is_open = False
-                    for d in range(3):
-                        for hi in range(2):
-                            q = p.copy()
-                            q[d] += 1 if hi else -1
-                            if 0 <= q[d] < n[d] or bc[2 * d + hi] == 0:
-                                q = q % n
-                                is_open |= m[q[2], q[1], q[0]] < 0
-                    assert not is_open or bool(wrote[i])
-        assert int(n_bad[1]) == 2 * int(n_bad[0])
+            # the planes that the flux registers read, and no others
+            need = flux_planes(n0, pos, l, bc, finer is not None)
+            assert need.any() == (l == 1 or finer is not None)
+            need = torch.from_numpy(need).to("cuda")
+            assert torch.equal(got[need], ff[need]) and not bool(got[~need].any())
+            count += 1
+        assert int(n_bad[1]) == count * int(n_bad[0])
