@@ -206,7 +206,11 @@ int hydro_branch_record(const void* U_pad_dev, void* U_out_dev, int64_t n_groups
  *               in the fused per-group kernel of hydro_advance (the default
  *               word in its own specialized copy) and need no workspace
  *               (their hydro_ext_workspace_bytes is 0; work_dev may be NULL);
- *               CTU, PPM and dual energy run as a chain of kernels through it
+ *               CTU, PPM and dual energy run in a fused march of their own
+ *               (CTU in two passes, the first solves' flux differences
+ *               between them in work_dev; the others use none of it) or,
+ *               for a few groups only (at most 5, CTU with PPM 40), as a chain
+ *               of kernels through it: the same bits, one workspace size
  *   n_bad_dev   as for hydro_advance (faces with unphysical input states plus
  *               updated cells with rho <= 0 or p <= 0)
  *   face_flux_dev  optional [G][9][5][16][16] output: the fluxes the update
@@ -604,7 +608,10 @@ int hydro_gather_ghost_adjoint(const void* g_pad_dev, void* g_level_dev, int32_t
                                int32_t ghost, int32_t dtype, const int32_t* bc_host, void* stream);
 
 /* Launch shapes of hydro_advance_level.  Every shape runs the same per-cell
- * arithmetic in the same order, so all give bit-identical results; they
+ * arithmetic in the same order, so all give bit-identical results.  A shape
+ * that the caller sets runs exactly as set; the default and tuned ones stand
+ * for levels that fill the chip, and a level of few groups has several
+ * workgroups share a group then (one z segment each, the same bits).  They
  * differ in the register budget the compiler was given (occupancy, bit 1),
  * in the order groups are dealt to workgroups (bit 0: plain, or blocked so
  * that each of the 8 XCDs sweeps a contiguous range of groups and finds

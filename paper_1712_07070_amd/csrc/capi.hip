@@ -246,8 +246,8 @@ bool fused_ext_scheme(const gh::ExtOpts& o) {
 // The other MHM + PLM words (any limiter, primitive or characteristic
 // variables, HLLC / Roe / HLLE, either wave-speed option, second or first
 // order; no dual energy) run in the same fused kernel with run-time options,
-// also without a workspace; CTU, PPM and dual energy take the chain of
-// per-cell / per-face kernels.
+// also without a workspace; CTU, PPM and dual energy take the march or the
+// chain of kernels of scheme_ext.hip.
 bool fused_plm_scheme(const gh::ExtOpts& o) { return !o.ctu && !o.ppm && !o.de; }
 
 template <typename T>

@@ -3,8 +3,8 @@
 // variables, PPM reconstruction, the HLLE and Roe Riemann solvers (Roe
 // switching to HLLC when a state between its waves is unphysical), and the
 // first-order recomputations of the procedure for unphysical results.  Used
-// by the multi-pass kernels of scheme_ext.hip; the default scheme's fused
-// kernels keep hydro_device.h only.
+// by the march of ext_march.h, the kernels of scheme_ext.hip and the other
+// words of the fused PLM march; the default scheme keeps hydro_device.h only.
 #pragma once
 
 #include "hydro_device.h"

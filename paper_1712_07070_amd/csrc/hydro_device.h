@@ -1,8 +1,8 @@
 // Device-side arithmetic of the MHM + PLM + HLLC step (GAMER-2, Sec. 2.2).
 //
 // Everything here is __device__ __forceinline__ and templated on the floating
-// type T (double or float).  Values are carried in registers; the kernels in
-// mhm_fwd.hip decide what is staged in LDS.  Every expression has a single
+// type T (double or float).  Values are carried in registers; the kernels
+// decide what is staged in LDS.  Every expression has a single
 // source form, and the library is built with -ffp-contract=on, so each
 // inlined copy of a function rounds identically: a face computed by two
 // workgroups (the shared face of neighbouring groups) gets bitwise-identical
