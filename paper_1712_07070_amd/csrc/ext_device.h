@@ -39,8 +39,9 @@ struct ExtOpts {
 // 256^3 FP64 characteristic step 1.76 ms, against 1.92 without); else the
 // divisions follow each other without branches, their latencies overlapped,
 // skipped together where no variable has a slope (the PPM march, three times
-// the slopes: 12 x 13 x 13 groups of noise 1.83 -> 1.61 ms).  The same values
-// either way.
+// the slopes: 12 x 13 x 13 groups of noise 1.83 -> 1.61 ms; the chain of kernels
+// on a few groups, bound by its latencies: 3 groups FP32 CTU + hybrid 37 -> 34
+// us, 8 to 10% on the others).  The same values either way.
 template <int K, bool kSkip, typename T>
 __device__ __forceinline__ void ext_limit_k(const T dm[K], const T dp[K], const T dc[K], T theta, int lim, T s[K]) {
   if constexpr (kSkip) {
@@ -202,7 +203,7 @@ __device__ __forceinline__ void ext_face_values(const T W[5][5], const Gas<T>& g
   }
   if (!o.ppm) {
     T s[5];
-    ext_slopes<D>(W[1], W[2], W[3], g, o, s);
+    ext_slopes<D, false>(W[1], W[2], W[3], g, o, s);
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       Wf[0][q] = W[2][q] - T(0.5) * s[q];
@@ -211,9 +212,9 @@ __device__ __forceinline__ void ext_face_values(const T W[5][5], const Gas<T>& g
     return;
   }
   T sm[5], s0[5], sp[5];
-  ext_slopes<D>(W[0], W[1], W[2], g, o, sm);
-  ext_slopes<D>(W[1], W[2], W[3], g, o, s0);
-  ext_slopes<D>(W[2], W[3], W[4], g, o, sp);
+  ext_slopes<D, false>(W[0], W[1], W[2], g, o, sm);
+  ext_slopes<D, false>(W[1], W[2], W[3], g, o, s0);
+  ext_slopes<D, false>(W[2], W[3], W[4], g, o, sp);
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
     Wf[0][q] = ppm_interface(W[1][q], W[2][q], sm[q], s0[q]);
