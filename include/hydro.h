@@ -209,7 +209,7 @@ int hydro_branch_record(const void* U_pad_dev, void* U_out_dev, int64_t n_groups
  *               CTU, PPM and dual energy run in a fused march of their own
  *               (CTU in two passes, the first solves' flux differences
  *               between them in work_dev; the others use none of it) or,
- *               for a few groups only (at most 5, CTU with PPM 40), as a chain
+ *               for a few groups only (at most 8, CTU with PPM 48), as a chain
  *               of kernels through it: the same bits, one workspace size
  *   n_bad_dev   as for hydro_advance (faces with unphysical input states plus
  *               updated cells with rho <= 0 or p <= 0)

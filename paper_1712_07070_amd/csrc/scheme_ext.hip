@@ -400,17 +400,20 @@ hipError_t chain_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<
 }
 
 // The march's iterations are serial, each with barriers and a chain of
-// dependent arithmetic, so a step takes it at least 20-26 us (MHM), 33-38 (CTU
-// with PLM), 52-68 (CTU with PPM) however few the groups; the chain's kernels
+// dependent arithmetic, so a step takes it at least 21-34 us (MHM), 31-42 (CTU
+// with PLM), 53-75 (CTU with PPM) however few the groups; the chain's kernels
 // run one cell or face per thread.  Measured, chain / march in us: MHM + PPM
-// FP64 4 groups 26.9 / 26.1, FP32 1 group 20.0 / 20.4, 4 groups 20.9 / 20.4;
-// with dual energy FP64 4 groups 31.7 / 32.8, 8 groups 35.1 / 33.0; CTU + PLM
-// FP64 4 groups 36.8 / 38.6, 8 groups 43.0 / 41.4, FP32 4 groups 29.0 / 33.2, 8
-// groups 34.8 / 33.7; CTU + PPM FP64 32 groups 103 / 112, 64 groups 183 / 170,
-// FP32 32 groups 61 / 63, 64 groups 97 / 82.
+// FP64 4 groups 24.7 / 26.0, 6 groups 27.7 / 26.2, FP32 6 groups 20.8 / 21.6, 8
+// groups 22.1 / 21.6; with dual energy FP64 10 groups 33.3 / 34.2, 12 groups
+// 42.9 / 34.8, FP32 8 groups 24.8 / 26.3, 10 groups 26.5 / 26.4; CTU + PLM FP64
+// 4 groups 36.2 / 36.2, 6 groups 40.2 / 36.7, FP32 6 groups 31.3 / 31.5, 8
+// groups 33.6 / 31.4, on characteristic variables FP64 8 groups 42.9 / 44.5, 12
+// groups 49.0 / 47.5, FP32 8 groups 34.5 / 34.9, 10 groups 36.7 / 35.4; CTU +
+// PPM FP64 48 groups 134 / 143, 56 groups 153 / 145, FP32 48 groups 75 / 76, 56
+// groups 83 / 81.
 bool use_chain(int64_t G, const ExtOpts& o) {
-  if (o.ctu) return G <= (o.ppm ? 40 : 6);
-  return G <= (o.de ? 5 : 2);
+  if (o.ctu) return G <= (o.ppm ? 48 : o.chr ? 8 : 5);
+  return G <= (o.de ? 8 : 4);
 }
 
 template <typename T, int NF, bool kPpm>

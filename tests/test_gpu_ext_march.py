@@ -58,7 +58,8 @@ def same(a, b):
                                     ("plm-char-vanleer-dual", 7), ("plm-char-vanleer-dual", 260), ("ctu-roe", 7),
                                     ("ctu-roe", 33), ("ctu-roe", 100), ("ctu-roe", 200), ("ctu-roe", 515),
                                     ("ctu-char-hlle-dual", 60), ("ctu-ppm-vanalbada", 41), ("ctu-ppm-vanalbada", 260),
-                                    ("ctu-ppm-roe-dual", 90)])
+                                    ("ctu-ppm-roe-dual", 90), ("ppm-hlle-davis-dual", 9), ("plm-char-vanleer-dual", 9),
+                                    ("ctu-char-hlle-dual", 9), ("ctu-ppm-vanalbada", 49)])
 def test_march_equals_chain_bitwise(hydro, dtype, name, G):
     word, ghost = words(hydro)[name]
     print("ext march", name, G, dtype, flush=True)
