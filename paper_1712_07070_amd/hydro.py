@@ -1052,7 +1052,6 @@ class AmrSolver:
         # the default words step a level from its own storage (hydro_amr_advance),
         # alternating between the caller's tensor and `alt`
         self.direct = (self.scheme & ~(WAVESPEED_DAVIS | FIRST_ORDER)) == SCHEME_MHM_PLM_HLLC
-        self.cur = [0] * self.nl
         maps_np = []
         for l, p in enumerate(positions):
             p = np.ascontiguousarray(p, np.int32).reshape(-1, 3)
@@ -1116,7 +1115,7 @@ class AmrSolver:
         the hierarchy by n_coarse steps in place.  Nothing runs at capture."""
         return Graph(ctx).capture(lambda: [self.step(dt0) for _ in range(n_coarse)])
 
-    def _advance(self, l, dt, cold, cnew, a, R_parent):
+    def _advance(self, l, dt, cold, cnew, a, R_parent, substep=0):
         lib, s = load(), _stream()
         code = _dtype_code(self.U[l])
         dx = self.dx0 / 2 ** l
@@ -1125,14 +1124,16 @@ class AmrSolver:
         oldp = None if cold is None else _dev(cold, "cold")
         newp = None if cnew is None else _dev(cnew, "cnew")
         if self.direct:
-            # the old states stay where they are (level 0 takes one substep: they
-            # are copied aside, so that the new ones land in the caller's tensor)
+            # the old states stay where they are: a level's first substep goes from
+            # the caller's tensor to `alt`, its second one back (level 0 takes one:
+            # the old states are copied aside, so that the new ones land in the
+            # caller's tensor).  Nothing is kept between steps, so that a step
+            # that raises does not change what the next one reads.
             if l == 0:
                 old, new = self.alt[0], self.U[0]
                 old.copy_(new)
             else:
-                old, new = (self.U[l], self.alt[l]) if self.cur[l] == 0 else (self.alt[l], self.U[l])
-                self.cur[l] ^= 1
+                old, new = (self.U[l], self.alt[l]) if substep == 0 else (self.alt[l], self.U[l])
             src = self._lvl(l, old)
             nxt = ctypes.byref(self._lvl(l + 1)) if l + 1 < self.nl else None
             st = lib.hydro_amr_advance(ctypes.byref(src), cptr, oldp, newp, float(a), self._bcarr, self.ghost, code,
@@ -1158,8 +1159,8 @@ class AmrSolver:
         if l + 1 < self.nl:
             R = self.reg[l + 1]
             R.zero_()
-            self._advance(l + 1, 0.5 * dt, old, new, 0.0, R)
-            self._advance(l + 1, 0.5 * dt, old, new, 0.5, R)
+            self._advance(l + 1, 0.5 * dt, old, new, 0.0, R, 0)
+            self._advance(l + 1, 0.5 * dt, old, new, 0.5, R, 1)
             child = self._lvl(l + 1)   # two substeps: back in its own tensor
             _check(lib.hydro_amr_restrict(ctypes.byref(child), ctypes.byref(fine), code, s), "hydro_amr_restrict")
             st = lib.hydro_amr_fixup(ctypes.byref(fine), ctypes.byref(child), _dev(self.flux[l], "flux"),
