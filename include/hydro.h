@@ -495,10 +495,12 @@ typedef struct {
 } hydro_level_t;
 
 /* hydro_advance_batched -- one MHM step of every group of n_levels levels in
- * ONE persistent launch (Sec. 2.1: levels of an AMR hierarchy advance with
- * their own dt; here their groups are pooled).  Workgroups take (level, group)
- * items from a device work counter until all are done; results are
- * bit-identical to one hydro_advance_level call per level.
+ * ONE launch (Sec. 2.1: levels of an AMR hierarchy advance with their own dt;
+ * here their groups are pooled).  Persistent workgroups take (level, group)
+ * items from a device work counter until all are done; few groups
+ * (hydro_batched_segments > 1) are shared by several workgroups each, without
+ * a queue, unless the caller set the shape or the grid.  Results are
+ * bit-identical to one hydro_advance_level call per level either way.
  *   levels_host  n_levels (1..8) entries in host memory; no output may overlap
  *                any input or another output
  *   dtype, gamma, scheme, theta, n_bad_dev: as for hydro_advance
@@ -516,7 +518,10 @@ typedef struct {
  * ...; 3: one queue per XCD, each serving level by level one of 8
  * contiguous blocks of the level's groups in column-tile order (the range
  * the XCD-blocked column-tile level step gives that XCD), with stealing);
- * hydro_set_batched_variant / hydro_get_batched_variant select and read it,
+ * hydro_set_batched_variant / hydro_get_batched_variant select and read it
+ * (for every launch of the dtype, in place of the tuned shapes);
+ * hydro_set_batched_tuned selects one as a tuner's choice, which stands for
+ * launches that fill the chip (few groups may be split under it);
  * hydro_autotune_batched times all of them on the given levels (two passes
  * of 1 untimed + `reps` timed launches per shape, a shape's time is the
  * smaller of its two means; SYNCHRONOUS; the outputs are overwritten;
@@ -543,9 +548,24 @@ int hydro_advance_batched_noalloc(hydro_ctx* ctx, const hydro_level_t* levels_ho
                                   double gamma, int32_t scheme, double theta, int32_t* n_bad_dev, int32_t grid,
                                   void* stream);
 int hydro_set_batched_variant(hydro_ctx* ctx, int32_t dtype, int32_t variant);
+int hydro_set_batched_tuned(hydro_ctx* ctx, int32_t dtype, int32_t variant);
 int hydro_get_batched_variant(hydro_ctx* ctx, int32_t dtype);
 int hydro_autotune_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels, int32_t dtype, double gamma,
                            uint32_t* work_dev, int32_t reps, float* times_ms_host, void* stream);
+
+/* How many workgroups (z segments) share a group in a step of the default
+ * words, from the number of groups; 1: whole groups.  Host queries, nothing is
+ * launched; a shape that the caller set, not a tuner, runs whole groups.
+ *   hydro_padded_segments   hydro_advance, and hydro_advance_ext with any
+ *                           MHM + PLM word
+ *   hydro_level_segments    hydro_advance_level with (with_cfl) CFL outputs,
+ *                           (with_patch_dt) dt_patch_next_dev among them
+ *   hydro_batched_segments  hydro_advance_batched(_noalloc) with grid 0
+ * HYDRO_EINVAL / HYDRO_ENOTUNED where the launch would return it for these. */
+int hydro_padded_segments(int64_t n_groups, int32_t dtype);
+int hydro_level_segments(hydro_ctx* ctx, int32_t ngx, int32_t ngy, int32_t ngz, int32_t dtype, int32_t with_cfl,
+                         int32_t with_patch_dt);
+int hydro_batched_segments(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels, int32_t dtype);
 
 /* Graph capture of a sequence of library calls (e.g. a level's substeps or
  * the stages of a coarse step), replayed without per-launch host overhead.

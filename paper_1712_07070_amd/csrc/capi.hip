@@ -88,9 +88,14 @@ std::string batched_key(int32_t dtype, const hydro_level_t* lv, int n) {
 }
 
 // The shape a launch uses: a tuned selection for this key, else the one set
-// explicitly, else (unless the context requires tuning) the default.
-// explicit_sel points into the context and is read under its lock.
-int select_shape(hydro_ctx* c, const std::string& key, const int* explicit_sel, int fallback, int* out) {
+// for the context, else (unless the context requires tuning) the default.
+// `sel` and `by_caller` point into the context and are read under its lock.
+// *exact: the shape is the caller's own (hydro_set_*_variant, not a tuner's
+// choice), so exactly that shape runs.  A tuned or default shape stands for
+// whole groups, and a launch of few groups may split them (plm_segments).
+int select_shape(hydro_ctx* c, const std::string& key, const int* sel, int fallback, int* out,
+                 const bool* by_caller = nullptr, bool* exact = nullptr) {
+  if (exact != nullptr) *exact = false;
   if (c == nullptr) {
     *out = fallback;
     return HYDRO_OK;
@@ -101,8 +106,9 @@ int select_shape(hydro_ctx* c, const std::string& key, const int* explicit_sel, 
     *out = it->second;
     return HYDRO_OK;
   }
-  if (*explicit_sel >= 0) {
-    *out = *explicit_sel;
+  if (*sel >= 0) {
+    *out = *sel;
+    if (exact != nullptr) *exact = *by_caller;
     return HYDRO_OK;
   }
   if (c->require_tuned) return HYDRO_ENOTUNED;
@@ -110,19 +116,14 @@ int select_shape(hydro_ctx* c, const std::string& key, const int* explicit_sel, 
   return HYDRO_OK;
 }
 
-// Whether the caller set the level step's shape itself (hydro_set_variant):
-// then exactly that shape runs.  A tuned or default shape stands for whole
-// groups, and a level of few groups may split them (plm_segments).
-bool shape_is_explicit(hydro_ctx* c, int32_t dtype, bool with_cfl) {
-  if (c == nullptr) return false;
-  std::lock_guard<std::mutex> lk(c->mu);
-  return c->level_explicit[dtype][with_cfl ? 1 : 0];
+int level_shape(hydro_ctx* c, int32_t dtype, bool with_cfl, int ngx, int ngy, int ngz, int* variant, bool* exact) {
+  return select_shape(c, level_key(dtype, with_cfl, ngx, ngy, ngz), c ? &c->level_sel[dtype][with_cfl ? 1 : 0] : nullptr,
+                      kDefaultLevelVariant, variant, c ? &c->level_explicit[dtype][with_cfl ? 1 : 0] : nullptr, exact);
 }
 
-bool batched_is_explicit(hydro_ctx* c, int32_t dtype) {
-  if (c == nullptr) return false;
-  std::lock_guard<std::mutex> lk(c->mu);
-  return c->batched_explicit[dtype];
+int batched_shape(hydro_ctx* c, int32_t dtype, const hydro_level_t* lv, int n, int* variant, bool* exact) {
+  return select_shape(c, batched_key(dtype, lv, n), c ? &c->batched_sel[dtype] : nullptr, kDefaultBatchedVariant,
+                      variant, c ? &c->batched_explicit[dtype] : nullptr, exact);
 }
 
 // Tuning cache: a JSON object {"version": 1, "entries": {"<key>": <shape>, ...}}.
@@ -263,11 +264,21 @@ gh::Gas<T> make_gas(double gamma, double theta, double dt, double dx) {
   return g;
 }
 
+// z segments per group of a batched launch whose shape is not the caller's own.
+int batched_split(const hydro_level_t* lv, int32_t n_levels, int32_t dtype) {
+  int64_t total = 0;
+  bool patches = false;
+  for (int l = 0; l < n_levels; ++l) {
+    total += int64_t(lv[l].ngx) * lv[l].ngy * lv[l].ngz;
+    patches = patches || lv[l].dt_patch_next_dev != nullptr;
+  }
+  return dtype == HYDRO_F64 ? gh::plm_segments<double>(total, patches) : gh::plm_segments<float>(total, patches);
+}
+
 template <typename T>
 int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_t scheme, double theta,
                  int32_t* n_bad_dev, uint32_t* work_dev, int32_t grid, int variant, bool split, hipStream_t s) {
   gh::BatchArgs<T> a;
-  bool patches = false;
   a.n_levels = n_levels;
   a.cfl = 0;
   long long total = 0;
@@ -292,7 +303,6 @@ int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_
     b.c_cfl_dx = lv[l].c_cfl * lv[l].dx;
     b.fold_scale = lv[l].dt_next_scale == 0.0 ? 1.0 : lv[l].dt_next_scale;
     a.cfl = a.cfl || b.dt_patch != nullptr || b.dt_min != nullptr || b.reset != nullptr;
-    patches = patches || b.dt_patch != nullptr;
     total += (long long)lv[l].ngx * lv[l].ngy * lv[l].ngz;
   }
   for (int l = n_levels; l < gh::kMaxLevels; ++l) {
@@ -309,7 +319,7 @@ int batched_impl(const hydro_level_t* lv, int32_t n_levels, double gamma, int32_
   const int fo = (scheme & HYDRO_FIRST_ORDER) ? 1 : 0, ws = (scheme >> 8) & 3;
   // few groups: shared by several workgroups each, without a queue (unless the
   // caller chose the shape or the grid itself)
-  const int segs = split && grid == 0 ? gh::plm_segments<T>(total, patches) : 1;
+  const int segs = split && grid == 0 ? batched_split(lv, n_levels, sizeof(T) == 8 ? HYDRO_F64 : HYDRO_F32) : 1;
   if (segs > 1) return device_status(gh::launch_mhm_batched_seg<T>(a, gas, fo, ws, n_bad_dev, segs, s));
   // work_dev NULL: the allocation-free entry point (the library's own counters)
   if (work_dev == nullptr)
@@ -483,6 +493,20 @@ int batched_launch(const hydro_level_t* levels_host, int32_t n_levels, int32_t d
     return batched_impl<double>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, split,
                                 s);
   return batched_impl<float>(levels_host, n_levels, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant, split, s);
+}
+
+// One shape for every batched launch of a dtype, in place of the tuned ones;
+// by_caller: as set, else like a tuned one.
+int set_batched(hydro_ctx* ctx, int32_t dtype, int32_t variant, bool by_caller) {
+  if (ctx == nullptr || (dtype != HYDRO_F64 && dtype != HYDRO_F32)) return HYDRO_EINVAL;
+  if (variant < 0 || variant >= gh::kBatchedVariants) return HYDRO_EINVAL;
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  ctx->batched_sel[dtype] = variant;
+  ctx->batched_explicit[dtype] = by_caller;
+  const std::string prefix = std::string("batched/") + dtype_name(dtype) + "/";
+  for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
+    it = it->first.compare(0, prefix.size(), prefix) == 0 ? ctx->tuned.erase(it) : std::next(it);
+  return HYDRO_OK;
 }
 
 // Preference among launch shapes that time as ties: XCD-blocked before
@@ -1021,9 +1045,9 @@ int hydro_advance_level_fallback(hydro_ctx* ctx, const void* level_in_dev, void*
     return HYDRO_EINVAL;
   const bool fused = valid_scheme(scheme, theta);
   int variant = 0;
+  bool exact = false;
   if (fused) {
-    st = select_shape(ctx, level_key(dtype, false, ngx, ngy, ngz), ctx ? &ctx->level_sel[dtype][0] : nullptr,
-                      kDefaultLevelVariant, &variant);
+    st = level_shape(ctx, dtype, false, ngx, ngy, ngz, &variant, &exact);
     if (st != HYDRO_OK) return st;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1036,7 +1060,7 @@ int hydro_advance_level_fallback(hydro_ctx* ctx, const void* level_in_dev, void*
     if (e != hipSuccess) return device_status(e);
     if (fused) {
       st = level_launch(level_in_dev, level_out_dev, geo, dtype, dt, dx, gamma, scheme, theta, nullptr, cnt + 3, 0.0,
-                        nullptr, nullptr, nullptr, variant, !shape_is_explicit(ctx, dtype, false), s);
+                        nullptr, nullptr, nullptr, variant, !exact, s);
     } else {
       e = dtype == HYDRO_F64
               ? gh::launch_fill_ghosts(static_cast<const double*>(level_in_dev), reinterpret_cast<double*>(pad), ngx,
@@ -1084,12 +1108,12 @@ int hydro_advance_level(hydro_ctx* ctx, const void* level_dev, void* level_out_d
   if (st != HYDRO_OK) return st;
   const bool with_cfl = dt_next_dev != nullptr || dt_patch_next_dev != nullptr || dt_reset_dev != nullptr;
   int variant = 0;
-  st = select_shape(ctx, level_key(dtype, with_cfl, ngx, ngy, ngz),
-                    ctx ? &ctx->level_sel[dtype][with_cfl ? 1 : 0] : nullptr, kDefaultLevelVariant, &variant);
+  bool exact = false;
+  st = level_shape(ctx, dtype, with_cfl, ngx, ngy, ngz, &variant, &exact);
   if (st != HYDRO_OK) return st;
   return level_launch(level_dev, level_out_dev, geo, dtype, dt, dx, gamma, scheme, theta, dt_dev, n_bad_dev, c_cfl,
-                      dt_next_dev, dt_patch_next_dev, dt_reset_dev, variant,
-                      !shape_is_explicit(ctx, dtype, with_cfl), static_cast<hipStream_t>(stream));
+                      dt_next_dev, dt_patch_next_dev, dt_reset_dev, variant, !exact,
+                      static_cast<hipStream_t>(stream));
 }
 
 int hydro_num_variants(void) { return gh::kLevelVariants; }
@@ -1199,11 +1223,11 @@ int hydro_advance_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int3
   int st = validate_levels(levels_host, n_levels, dtype);
   if (st != HYDRO_OK) return st;
   int variant = 0;
-  st = select_shape(ctx, batched_key(dtype, levels_host, n_levels), ctx ? &ctx->batched_sel[dtype] : nullptr,
-                    kDefaultBatchedVariant, &variant);
+  bool exact = false;
+  st = batched_shape(ctx, dtype, levels_host, n_levels, &variant, &exact);
   if (st != HYDRO_OK) return st;
   return batched_launch(levels_host, n_levels, dtype, gamma, scheme, theta, n_bad_dev, work_dev, grid, variant,
-                        !batched_is_explicit(ctx, dtype), static_cast<hipStream_t>(stream));
+                        !exact, static_cast<hipStream_t>(stream));
 }
 
 int hydro_advance_batched_noalloc(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels,
@@ -1215,23 +1239,19 @@ int hydro_advance_batched_noalloc(hydro_ctx* ctx, const hydro_level_t* levels_ho
   int st = validate_levels(levels_host, n_levels, dtype);
   if (st != HYDRO_OK) return st;
   int variant = 0;
-  st = select_shape(ctx, batched_key(dtype, levels_host, n_levels), ctx ? &ctx->batched_sel[dtype] : nullptr,
-                    kDefaultBatchedVariant, &variant);
+  bool exact = false;
+  st = batched_shape(ctx, dtype, levels_host, n_levels, &variant, &exact);
   if (st != HYDRO_OK) return st;
   return batched_launch(levels_host, n_levels, dtype, gamma, scheme, theta, n_bad_dev, nullptr, grid, variant,
-                        !batched_is_explicit(ctx, dtype), static_cast<hipStream_t>(stream));
+                        !exact, static_cast<hipStream_t>(stream));
 }
 
 int hydro_set_batched_variant(hydro_ctx* ctx, int32_t dtype, int32_t variant) {
-  if (ctx == nullptr || (dtype != HYDRO_F64 && dtype != HYDRO_F32)) return HYDRO_EINVAL;
-  if (variant < 0 || variant >= gh::kBatchedVariants) return HYDRO_EINVAL;
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  ctx->batched_sel[dtype] = variant;
-  ctx->batched_explicit[dtype] = true;
-  const std::string prefix = std::string("batched/") + dtype_name(dtype) + "/";
-  for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
-    it = it->first.compare(0, prefix.size(), prefix) == 0 ? ctx->tuned.erase(it) : std::next(it);
-  return HYDRO_OK;
+  return set_batched(ctx, dtype, variant, true);
+}
+
+int hydro_set_batched_tuned(hydro_ctx* ctx, int32_t dtype, int32_t variant) {
+  return set_batched(ctx, dtype, variant, false);
 }
 
 int hydro_get_batched_variant(hydro_ctx* ctx, int32_t dtype) {
@@ -1259,6 +1279,36 @@ int hydro_autotune_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int
     for (int var = 0; var < gh::kBatchedVariants; ++var) times_ms_host[var] = ms[var];
   record_tuned(ctx, batched_key(dtype, levels_host, n_levels), best);
   return best;
+}
+
+// ---------------------------------------------------------- work split ----
+int hydro_padded_segments(int64_t n_groups, int32_t dtype) {
+  if (n_groups < 0 || (dtype != HYDRO_F64 && dtype != HYDRO_F32)) return HYDRO_EINVAL;
+  return dtype == HYDRO_F64 ? gh::plm_segments<double>(n_groups, false) : gh::plm_segments<float>(n_groups, false);
+}
+
+int hydro_level_segments(hydro_ctx* ctx, int32_t ngx, int32_t ngy, int32_t ngz, int32_t dtype, int32_t with_cfl,
+                         int32_t with_patch_dt) {
+  if (!level_geom_ok(ngx, ngy, ngz) || (dtype != HYDRO_F64 && dtype != HYDRO_F32)) return HYDRO_EINVAL;
+  int variant = 0;
+  bool exact = false;
+  const int st = level_shape(ctx, dtype, with_cfl != 0 || with_patch_dt != 0, ngx, ngy, ngz, &variant, &exact);
+  if (st != HYDRO_OK) return st;
+  const int64_t G = int64_t(ngx) * ngy * ngz;
+  if (exact) return 1;
+  return dtype == HYDRO_F64 ? gh::plm_segments<double>(G, with_patch_dt != 0)
+                            : gh::plm_segments<float>(G, with_patch_dt != 0);
+}
+
+int hydro_batched_segments(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels, int32_t dtype) {
+  if (dtype != HYDRO_F64 && dtype != HYDRO_F32) return HYDRO_EINVAL;
+  int st = validate_levels(levels_host, n_levels, dtype);
+  if (st != HYDRO_OK) return st;
+  int variant = 0;
+  bool exact = false;
+  st = batched_shape(ctx, dtype, levels_host, n_levels, &variant, &exact);
+  if (st != HYDRO_OK) return st;
+  return exact ? 1 : batched_split(levels_host, n_levels, dtype);
 }
 
 // ------------------------------------------------------------- graphs ----

@@ -113,7 +113,11 @@ def load():
         "hydro_advance_batched": (i32, [P, P, i32, i32, f64, i32, f64, P, P, i32, P]),
         "hydro_advance_batched_noalloc": (i32, [P, P, i32, i32, f64, i32, f64, P, i32, P]),
         "hydro_set_batched_variant": (i32, [P, i32, i32]),
+        "hydro_set_batched_tuned": (i32, [P, i32, i32]),
         "hydro_get_batched_variant": (i32, [P, i32]),
+        "hydro_padded_segments": (i32, [i64, i32]),
+        "hydro_level_segments": (i32, [P, i32, i32, i32, i32, i32, i32]),
+        "hydro_batched_segments": (i32, [P, P, i32, i32]),
         "hydro_autotune_batched": (i32, [P, P, i32, i32, f64, P, i32, P, P]),
         "hydro_autotune_adjoint": (i32, [P, P, P, P, i32, i32, i32, P, i32, f64, f64, P, i64, i32, P, P]),
         "hydro_graph_begin": (i32, [P]),
@@ -590,7 +594,7 @@ def _levels_array(levels):
 
 def advance_batched(levels, gamma: float, work: torch.Tensor, theta: float = 1.5, scheme: int = SCHEME_MHM_PLM_HLLC,
                     n_bad: Optional[torch.Tensor] = None, grid: int = 0, ctx: Optional[Context] = None) -> None:
-    """One step of several levels in one persistent launch (hydro_advance_batched).
+    """One step of several levels in one launch (hydro_advance_batched).
 
     levels: sequence of (level_in, level_out, ng, bc, dt, dx[, dt_dev[, cfl]]),
     cfl an optional dict of the level's CFL outputs and dt scale (keys
@@ -636,8 +640,43 @@ def set_batched_variant(dtype, v: int, ctx: Optional[Context] = None) -> None:
            "hydro_set_batched_variant")
 
 
+def set_batched_tuned(dtype, v: int, ctx: Optional[Context] = None) -> None:
+    """set_batched_variant for a shape chosen by timing: it stands for launches
+    that fill the chip, and few groups may be split under it."""
+    _check(load().hydro_set_batched_tuned(_ctx(ctx), F64 if dtype == torch.float64 else F32, int(v)),
+           "hydro_set_batched_tuned")
+
+
 def get_batched_variant(dtype, ctx: Optional[Context] = None) -> int:
     return int(load().hydro_get_batched_variant(_ctx(ctx), F64 if dtype == torch.float64 else F32))
+
+
+def _segments(n: int, fn: str) -> int:
+    if n < 0:
+        raise HydroError(fn, n)
+    return int(n)
+
+
+def padded_segments(n_groups: int, dtype) -> int:
+    """Workgroups that share a group in advance / advance_ext with MHM + PLM
+    words (1: whole groups)."""
+    return _segments(load().hydro_padded_segments(int(n_groups), F64 if dtype == torch.float64 else F32),
+                     "hydro_padded_segments")
+
+
+def level_segments(ng: Sequence[int], dtype, with_cfl: bool = False, with_patch_dt: bool = False,
+                   ctx: Optional[Context] = None) -> int:
+    """Workgroups that share a group in advance_level."""
+    return _segments(load().hydro_level_segments(_ctx(ctx), int(ng[0]), int(ng[1]), int(ng[2]),
+                                                 F64 if dtype == torch.float64 else F32, int(with_cfl),
+                                                 int(with_patch_dt)), "hydro_level_segments")
+
+
+def batched_segments(levels, ctx: Optional[Context] = None) -> int:
+    """Workgroups that share a group in advance_batched (1: the queue)."""
+    arr, dtype = _levels_array(levels)
+    return _segments(load().hydro_batched_segments(_ctx(ctx), ctypes.cast(arr, ctypes.c_void_p), len(levels),
+                                                   F64 if dtype == torch.float64 else F32), "hydro_batched_segments")
 
 
 class Graph:
@@ -801,7 +840,7 @@ class MultiLevel:
             _, times = autotune_batched(ent, self.gamma, self.work, reps, ctx=self.ctx)
             total = [a + c * t for a, t in zip(total, times)]
         best = min(range(len(total)), key=total.__getitem__)
-        set_batched_variant(self.dtype, best, ctx=self.ctx)
+        set_batched_tuned(self.dtype, best, ctx=self.ctx)
         return best, total
 
     def capture(self, n_coarse: int = 2) -> Graph:
