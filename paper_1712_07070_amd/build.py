@@ -11,7 +11,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhydro.so")
 OBJ = os.path.join(ROOT, "_build")
-SOURCES = ["capi.hip", "mhm_fwd.hip", "mhm_fwd_g2.hip", "mhm_fwd_ext.hip", "mhm_seg.hip", "mhm_batched.hip", "mhm_adj.hip", "aux_kernels.hip", "scheme_ext.hip",
+SOURCES = ["capi.hip", "mhm_fwd.hip", "mhm_fwd_g2.hip", "mhm_fwd_ext.hip", "mhm_ext_first.hip",
+           "mhm_ext_lim0.hip", "mhm_ext_lim1.hip", "mhm_ext_lim2.hip", "mhm_ext_lim3.hip", "mhm_seg.hip",
+           "mhm_batched.hip", "mhm_adj.hip", "aux_kernels.hip", "scheme_ext.hip",
            "march_step.hip", "march_ctu_plm.hip", "march_ctu_ppm.hip", "fallback.hip", "amr.hip",
            "mhm_amr.hip"]
 

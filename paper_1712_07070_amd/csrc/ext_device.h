@@ -33,45 +33,42 @@ struct ExtOpts {
 //   1 van Leer            2 dm dp / (dm + dp)
 //   2 van Albada          dm dp (dm + dp) / (dm^2 + dp^2)
 //   3 hybrid              sgn(dc) min(generalized minmod, |van Leer|)
-// K variables at once, the (uniform) limiter selected once for all of them.
-// kSkip: each division inside its sign test, which a wave skips where no lane
-// has a slope (the PLM march on a shear layer, uniform but for one field:
-// 256^3 FP64 characteristic step 1.76 ms, against 1.92 without); else the
-// divisions follow each other without branches, their latencies overlapped,
-// skipped together where no variable has a slope (the PPM march, three times
-// the slopes: 12 x 13 x 13 groups of noise 1.83 -> 1.61 ms; the chain of kernels
-// on a few groups, bound by its latencies: 3 groups FP32 CTU + hybrid 37 -> 34
-// us, 8 to 10% on the others).  The same values either way.
+// K variables at once (the limiter is uniform, and a compile-time constant in
+// the PLM march of whole groups).
+// kSkip: each variable inside its sign test, which a wave skips where no lane
+// has a slope, and all of them behind one test of the wave (the PLM march: a
+// flow along one axis, or with a jump in one field, has most slopes zero);
+// else the divisions follow each other without branches, their latencies
+// overlapped, skipped together where no variable has a slope (the PPM march,
+// three times the slopes: 12 x 13 x 13 groups of noise 1.83 -> 1.61 ms; the
+// chain of kernels on a few groups, bound by its latencies: 3 groups FP32 CTU +
+// hybrid 37 -> 34 us, 8 to 10% on the others).  The same values either way.
+// For the PLM march's forms see mhm_fwd_ext.h.
 template <int K, bool kSkip, typename T>
 __device__ __forceinline__ void ext_limit_k(const T dm[K], const T dp[K], const T dc[K], T theta, int lim, T s[K]) {
   if constexpr (kSkip) {
-    if (lim == 1) {
+    bool some = false;
 #pragma unroll
-      for (int q = 0; q < K; ++q) {
-        s[q] = T(0);
-        if (dm[q] * dp[q] > T(0)) s[q] = Fp<T>::div(T(2) * dm[q] * dp[q], dm[q] + dp[q]);
-      }
-    } else if (lim == 2) {
+    for (int q = 0; q < K; ++q) some = some || dm[q] * dp[q] > T(0);
+    if (__builtin_amdgcn_ballot_w64(some) == 0) {
 #pragma unroll
-      for (int q = 0; q < K; ++q) {
-        s[q] = T(0);
-        if (dm[q] * dp[q] > T(0))
-          s[q] = Fp<T>::div(dm[q] * dp[q] * (dm[q] + dp[q]), dm[q] * dm[q] + dp[q] * dp[q]);
-      }
-    } else {
+      for (int q = 0; q < K; ++q) s[q] = T(0);
+      return;
+    }
 #pragma unroll
-      for (int q = 0; q < K; ++q) {
+    for (int q = 0; q < K; ++q) {
+      s[q] = T(0);
+      if (!(dm[q] * dp[q] > T(0))) continue;
+      if (lim == 1) {
+        s[q] = Fp<T>::div(T(2) * dm[q] * dp[q], dm[q] + dp[q]);
+      } else if (lim == 2) {
+        s[q] = Fp<T>::div(dm[q] * dp[q] * (dm[q] + dp[q]), dm[q] * dm[q] + dp[q] * dp[q]);
+      } else {
         T m = fmin_(theta * fabs_(dm[q]), fabs_(dc[q]));
         m = fmin_(m, theta * fabs_(dp[q]));
-        s[q] = dm[q] * dp[q] > T(0) ? m : T(0);
+        if (lim == 3) m = fmin_(m, fabs_(Fp<T>::div(T(2) * dm[q] * dp[q], dm[q] + dp[q])));
+        s[q] = copysign_(m, dc[q]);
       }
-      if (lim == 3) {
-#pragma unroll
-        for (int q = 0; q < K; ++q)
-          if (dm[q] * dp[q] > T(0)) s[q] = fmin_(s[q], fabs_(Fp<T>::div(T(2) * dm[q] * dp[q], dm[q] + dp[q])));
-      }
-#pragma unroll
-      for (int q = 0; q < K; ++q) s[q] = dm[q] * dp[q] > T(0) ? copysign_(s[q], dc[q]) : T(0);
     }
   } else {
     bool ok[K], some = false;

@@ -91,10 +91,6 @@ template <typename T>
 hipError_t launch_mhm_batched_seg(const BatchArgs<T>& args, const Gas<T>& gas, int first_order, int ws, int* n_bad,
                                   int segs, hipStream_t stream);
 struct ExtOpts;
-template <typename T>
-hipError_t launch_mhm_fwd_ext_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
-                                  const double* dt_dev, double dx, const ExtOpts& o, int* n_bad, hipStream_t stream,
-                                  T* face_flux, int segs);
 
 // One level of a batched launch: input / output level storage, geometry,
 // the level's dt/dx (or a device dt), and the index of its first work item.

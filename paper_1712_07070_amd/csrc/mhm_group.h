@@ -153,11 +153,13 @@ struct Smem {
 //                  the same half step with the slopes of ext_slopes and the
 //                  fluxes of riemann_any.
 struct DefaultScheme {};
-// kChr (0 / 1) fixes the characteristic projection at compile time and kRoe
-// the solver family (1: Roe, 0: HLLC or HLLE); -1 leaves either to run
-// time.  Each fixed combination is its own inlined copy, which carries only
-// the registers of its own options.
-template <int kChr = -1, int kRoe = -1>
+// kChr (0 / 1) fixes the characteristic projection at compile time, kRoe
+// the solver family (1: Roe, 0: HLLC or HLLE) and kLim the limiter of a
+// second-order step (0 .. 3) or a first-order one (kFirstOrder); -1 leaves it
+// to run time.  Each fixed combination is its own inlined copy, which carries
+// only the registers of its own options.
+constexpr int kFirstOrder = 4;
+template <int kChr = -1, int kRoe = -1, int kLim = -1>
 struct ExtSchemeT {
   ExtOpts o;
   __device__ __forceinline__ ExtOpts opts() const {
@@ -165,6 +167,10 @@ struct ExtSchemeT {
     if (kChr >= 0) r.chr = kChr;
     if (kRoe == 1) r.solver = 1;
     if (kRoe == 0) r.solver = o.solver == 2 ? 2 : 0;
+    if (kLim >= 0) {
+      r.lim = kLim;
+      r.first_order = kLim == kFirstOrder;
+    }
     return r;
   }
 };
@@ -179,8 +185,8 @@ __device__ __forceinline__ void scheme_half_step(const DefaultScheme&, const T W
 // The half step with full limited slopes s: face states Wc -+ s/2 (as the
 // oracle's face values), then hancock_states' conserved form, fluxes and
 // flux differences.
-template <typename T, int kChr, int kRoe>
-__device__ __forceinline__ void scheme_half_step(const ExtSchemeT<kChr, kRoe>& sch, const T Wc[5], const T Wn[3][2][5],
+template <typename T, int kChr, int kRoe, int kLim>
+__device__ __forceinline__ void scheme_half_step(const ExtSchemeT<kChr, kRoe, kLim>& sch, const T Wc[5], const T Wn[3][2][5],
                                                  const Gas<T>& g, bool, T Ut[3][2][5], unsigned*) {
   const ExtOpts o = sch.opts();
   T sum[5];
@@ -238,8 +244,8 @@ __device__ __forceinline__ bool scheme_flux(const DefaultScheme&, const T L[5], 
                                             T F[5], unsigned* rec) {
   return hllc_flux<D>(L, R, g, ws, F, rec);
 }
-template <int D, typename T, int kChr, int kRoe>
-__device__ __forceinline__ bool scheme_flux(const ExtSchemeT<kChr, kRoe>& sch, const T L[5], const T R[5],
+template <int D, typename T, int kChr, int kRoe, int kLim>
+__device__ __forceinline__ bool scheme_flux(const ExtSchemeT<kChr, kRoe, kLim>& sch, const T L[5], const T R[5],
                                             const Gas<T>& g, int, T F[5], unsigned*) {
   return riemann_any<D>(L, R, g, sch.opts(), F);
 }
@@ -250,8 +256,8 @@ __device__ __forceinline__ int scheme_flux2(const DefaultScheme&, const T L0[5],
                                             const T R1[5], const Gas<T>& g, int ws, T F0[5], T F1[5], unsigned* rec) {
   return hllc_flux2<D0, D1>(L0, R0, L1, R1, g, ws, F0, F1, rec);
 }
-template <int D0, int D1, typename T, int kChr, int kRoe>
-__device__ __forceinline__ int scheme_flux2(const ExtSchemeT<kChr, kRoe>& sch, const T L0[5], const T R0[5],
+template <int D0, int D1, typename T, int kChr, int kRoe, int kLim>
+__device__ __forceinline__ int scheme_flux2(const ExtSchemeT<kChr, kRoe, kLim>& sch, const T L0[5], const T R0[5],
                                             const T L1[5], const T R1[5], const Gas<T>& g, int, T F0[5], T F1[5],
                                             unsigned*) {
   const ExtOpts o = sch.opts();
@@ -340,13 +346,19 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
                                               double gamma_d, T* __restrict__ ff, unsigned* rec, const Z& zr, unsigned ff_planes) {
   const int cx = c.cx, cy = c.cy;
   int bad = 0;
-  // U^n of plane k-1 for its update at the end of this phase, issued first
-  // so that the load's latency overlaps the half step and the z-face solve
+  // What the update of plane k-1 at the end of this phase takes.  The default
+  // scheme has both early; the other words fetch them where they are used, since
+  // their solves need the registers (FP64 spills of the HLLC / Roe copies 6 / 28
+  // -> 0 / 9, 2048 groups 16% faster on average; only the differences late: 0 /
+  // 17 and 13%).
+  constexpr bool kEarly = std::is_same<Sch, DefaultScheme>::value;
+  // U^n of plane k-1, issued first so that the load's latency overlaps the
+  // half step and the z-face solve
   T Uold[5];
-  if (kI && k > zr.lo) load_cons<kI>(src, c.col, k - 1, Uold);
+  if (kEarly && kI && k > zr.lo) load_cons<kI>(src, c.col, k - 1, Uold);
   // x/y flux differences of plane k-1 (fluxes written last iteration)
   T acc[5];
-  if (kI && k > zr.lo) {
+  if (kEarly && kI && k > zr.lo) {
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
       acc[q] = sm.F[0][q][fxidx(cx + 1, cy)] - sm.F[0][q][fxidx(cx, cy)];
@@ -386,6 +398,7 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
     if (k >= zr.lo) {
       T Fz1[5];
       const int bz = scheme_flux<2>(sch, c.Uz, Ut[2][0], gas, ws, Fz1, rec);
+      if (!kEarly && k > zr.lo) load_cons<kI>(src, c.col, k - 1, Uold);
       bool own = true;
       if constexpr (!std::is_same<Z, ZAll>::value) own = k < zr.hi || zr.hi == 16;
       bad += own ? bz : 0;
@@ -396,6 +409,13 @@ __device__ __forceinline__ int fwd_col_states(const Sch& sch, FwdCol<T, kI, type
         for (int q = 0; q < 5; ++q) o[q * 256] = Fz1[q];
       }
       if (k > zr.lo) {
+        if (!kEarly) {
+#pragma unroll
+          for (int q = 0; q < 5; ++q) {
+            acc[q] = sm.F[0][q][fxidx(cx + 1, cy)] - sm.F[0][q][fxidx(cx, cy)];
+            acc[q] = acc[q] + (sm.F[1][q][fyidx(cx, cy + 1)] - sm.F[1][q][fyidx(cx, cy)]);
+          }
+        }
         // complete plane k-1: U^{n+1} = U^n - dt/dx [(x) + (y) + (z)]
         T Un[5];
 #pragma unroll

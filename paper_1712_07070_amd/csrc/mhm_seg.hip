@@ -3,7 +3,8 @@
 // workgroup per group leaves the chip idle below 256 groups (one per compute
 // unit), and a march of 18 iterations takes about 75 us (FP64) however few
 // the groups; a segment of n planes runs n + 2.  Same arithmetic, same bits.
-// Sources and outputs as in mhm_fwd.hip and mhm_fwd_ext.hip.
+// Sources and outputs as in mhm_fwd.hip; the other words' segments are in
+// mhm_fwd_ext.h.
 
 #include "mhm_group.h"
 
@@ -98,37 +99,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
   if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
 }
 
-template <typename T, bool kFlux, int kChr, int kRoe>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_padded_ext_seg_kernel(
-    const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
-    ExtOpts o, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
-  __shared__ Smem<T> sm;
-  __shared__ T stage[kFlux ? kFluxStage : 1];
-  set_dt(gas, dt_dev, dx);
-  const int g = int(blockIdx.x) / segs, n = 16 / segs, lo = (int(blockIdx.x) % segs) * n;
-  const int P = 16 + 2 * gh;
-  const PaddedSource<T> src{Upad + int64_t(g) * 5 * P * P * P, P, gh};
-  T* ff = kFlux ? face_flux + int64_t(g) * 9 * 5 * 256 : nullptr;
-  const ExtSchemeT<kChr, kRoe> sch{o};
-  const int bad = process_group<T, false>(src, Uout + int64_t(g) * 5 * 4096, gas, o.first_order, o.ws, sm, nullptr,
-                                          0.0, threadIdx.x, ff, nullptr, sch, ZPart{lo, lo + n}, stage);
-  if (n_bad != nullptr && bad != 0) atomicAdd(n_bad, bad);
-}
-
-template <typename T, bool kFlux>
-void launch_ext_seg(const T* U_pad, T* U_out, dim3 grid, int ghost, const Gas<T>& gas, const double* dt_dev, double dx,
-                    const ExtOpts& o, int* n_bad, hipStream_t stream, T* ff, int segs) {
-  const bool roe = o.solver == 1;
-  const dim3 block(kThreads);
-  if (o.chr) {
-    if (roe) hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 1, 1>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
-    else hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 1, 0>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
-  } else {
-    if (roe) hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 0, 1>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
-    else hipLaunchKernelGGL((mhm_padded_ext_seg_kernel<T, kFlux, 0, 0>), grid, block, 0, stream, U_pad, U_out, ghost, gas, dt_dev, dx, o, n_bad, ff, segs);
-  }
-}
-
 }  // namespace
 
 template <typename T>
@@ -172,26 +142,12 @@ hipError_t launch_mhm_fwd_seg(const T* U_pad, T* U_out, int n_groups, int ghost,
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_mhm_fwd_ext_seg(const T* U_pad, T* U_out, int n_groups, int ghost, const Gas<T>& gas,
-                                  const double* dt_dev, double dx, const ExtOpts& o, int* n_bad, hipStream_t stream,
-                                  T* face_flux, int segs) {
-  const dim3 grid(unsigned(n_groups * segs));
-  if (face_flux != nullptr)
-    launch_ext_seg<T, true>(U_pad, U_out, grid, ghost, gas, dt_dev, dx, o, n_bad, stream, face_flux, segs);
-  else
-    launch_ext_seg<T, false>(U_pad, U_out, grid, ghost, gas, dt_dev, dx, o, n_bad, stream, face_flux, segs);
-  return hipGetLastError();
-}
-
 #define GH_SEG_INST(T)                                                                                                \
   template hipError_t launch_mhm_level_seg<T>(const T*, T*, const LevelGeom&, const Gas<T>&, const double*, double,   \
                                               int, int, int*, const CflOut&, int, hipStream_t);                       \
   template hipError_t launch_mhm_batched_seg<T>(const BatchArgs<T>&, const Gas<T>&, int, int, int*, int, hipStream_t); \
   template hipError_t launch_mhm_fwd_seg<T>(const T*, T*, int, int, const Gas<T>&, const double*, double, int, int,   \
-                                            int*, hipStream_t, T*, int);                                              \
-  template hipError_t launch_mhm_fwd_ext_seg<T>(const T*, T*, int, int, const Gas<T>&, const double*, double,         \
-                                                const ExtOpts&, int*, hipStream_t, T*, int);
+                                            int*, hipStream_t, T*, int);
 GH_SEG_INST(double)
 GH_SEG_INST(float)
 #undef GH_SEG_INST
