@@ -209,8 +209,8 @@ int hydro_branch_record(const void* U_pad_dev, void* U_out_dev, int64_t n_groups
  *               CTU, PPM and dual energy run in a fused march of their own
  *               (CTU in two passes, the first solves' flux differences
  *               between them in work_dev; the others use none of it) or,
- *               for a few groups only (at most 8, CTU with PPM 48), as a chain
- *               of kernels through it: the same bits, one workspace size
+ *               for a few groups only (hydro_ext_uses_chain), as a chain of
+ *               kernels through it: the same bits, one workspace size
  *   n_bad_dev   as for hydro_advance (faces with unphysical input states plus
  *               updated cells with rho <= 0 or p <= 0)
  *   face_flux_dev  optional [G][9][5][16][16] output: the fluxes the update
@@ -561,8 +561,12 @@ int hydro_autotune_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int
  *   hydro_level_segments    hydro_advance_level with (with_cfl) CFL outputs,
  *                           (with_patch_dt) dt_patch_next_dev among them
  *   hydro_batched_segments  hydro_advance_batched(_noalloc) with grid 0
+ *   hydro_ext_uses_chain    1 if hydro_advance_ext runs n_groups (those of one
+ *                           chunk that work_dev holds) of this word as a chain of
+ *                           kernels through work_dev, else 0
  * HYDRO_EINVAL / HYDRO_ENOTUNED where the launch would return it for these. */
 int hydro_padded_segments(int64_t n_groups, int32_t dtype);
+int hydro_ext_uses_chain(int64_t n_groups, int32_t ghost, int32_t dtype, int32_t scheme);
 int hydro_level_segments(hydro_ctx* ctx, int32_t ngx, int32_t ngy, int32_t ngz, int32_t dtype, int32_t with_cfl,
                          int32_t with_patch_dt);
 int hydro_batched_segments(hydro_ctx* ctx, const hydro_level_t* levels_host, int32_t n_levels, int32_t dtype);

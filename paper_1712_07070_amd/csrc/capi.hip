@@ -1282,6 +1282,14 @@ int hydro_autotune_batched(hydro_ctx* ctx, const hydro_level_t* levels_host, int
 }
 
 // ---------------------------------------------------------- work split ----
+int hydro_ext_uses_chain(int64_t n_groups, int32_t ghost, int32_t dtype, int32_t scheme) {
+  gh::ExtOpts o;
+  if (n_groups < 0 || ghost > 16 || (dtype != HYDRO_F64 && dtype != HYDRO_F32) ||
+      !valid_ext_scheme(scheme, 1.5, ghost, &o))
+    return HYDRO_EINVAL;
+  return !fused_plm_scheme(o) && gh::ext_uses_chain(n_groups, dtype == HYDRO_F64, o) ? 1 : 0;
+}
+
 int hydro_padded_segments(int64_t n_groups, int32_t dtype) {
   if (n_groups < 0 || (dtype != HYDRO_F64 && dtype != HYDRO_F32)) return HYDRO_EINVAL;
   return dtype == HYDRO_F64 ? gh::plm_segments<double>(n_groups, false) : gh::plm_segments<float>(n_groups, false);

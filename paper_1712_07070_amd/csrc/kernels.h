@@ -194,6 +194,8 @@ hipError_t launch_mhm_record(const double* U_pad, double* U_out, int64_t n_group
 // elements of T for G groups of ghost width `ghost`, and the step.
 struct ExtOpts;
 int64_t ext_workspace_elems(int64_t n_groups, int ghost, const ExtOpts& o);
+// Whether the step of G groups runs as the chain of kernels (else: the march).
+bool ext_uses_chain(int64_t G, bool fp64, const ExtOpts& o);
 // face_flux (optional): [G][9][5][256] fluxes on the patch-boundary faces.
 template <typename T>
 hipError_t launch_ext_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<T>& gas, const double* dt_dev,

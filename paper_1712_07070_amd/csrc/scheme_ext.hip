@@ -4,7 +4,7 @@
 //
 // Two paths with the same arithmetic (bit-identical results): the march of
 // ext_march.h, one workgroup per z segment of a group, and, for the few
-// groups that leave it waiting on its own latency (use_chain), a chain of
+// groups that leave it waiting on its own latency (ext_uses_chain), a chain of
 // kernels with one thread per cell or face, passing primitive states, face
 // states and fluxes through the caller's workspace in HBM in the order the
 // step defines them:
@@ -400,20 +400,40 @@ hipError_t chain_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<
 }
 
 // The march's iterations are serial, each with barriers and a chain of
-// dependent arithmetic, so a step takes it at least 21-34 us (MHM), 31-42 (CTU
-// with PLM), 53-75 (CTU with PPM) however few the groups; the chain's kernels
-// run one cell or face per thread.  Measured, chain / march in us: MHM + PPM
-// FP64 4 groups 24.7 / 26.0, 6 groups 27.7 / 26.2, FP32 6 groups 20.8 / 21.6, 8
-// groups 22.1 / 21.6; with dual energy FP64 10 groups 33.3 / 34.2, 12 groups
-// 42.9 / 34.8, FP32 8 groups 24.8 / 26.3, 10 groups 26.5 / 26.4; CTU + PLM FP64
-// 4 groups 36.2 / 36.2, 6 groups 40.2 / 36.7, FP32 6 groups 31.3 / 31.5, 8
-// groups 33.6 / 31.4, on characteristic variables FP64 8 groups 42.9 / 44.5, 12
-// groups 49.0 / 47.5, FP32 8 groups 34.5 / 34.9, 10 groups 36.7 / 35.4; CTU +
-// PPM FP64 48 groups 134 / 143, 56 groups 153 / 145, FP32 48 groups 75 / 76, 56
-// groups 83 / 81.
-bool use_chain(int64_t G, const ExtOpts& o) {
-  if (o.ctu) return G <= (o.ppm ? 48 : o.chr ? 8 : 5);
-  return G <= (o.de ? 8 : 4);
+// dependent arithmetic, so a step takes it at least 13-36 us (MHM), 30-52 (CTU
+// with PLM), 52-97 (CTU with PPM) however few the groups; the chain's kernels
+// run one cell or face per thread.  The lines follow the measured times (four
+// words each, from generalized minmod + HLLC to van Leer + Roe).  The FP64 march
+// runs 16 segments up to 32 groups (from 17 on two workgroups to a compute unit),
+// 8 up to 64, then 4 (march_segments), so beyond 16 and 64 groups the chain is
+// ahead once more for some words.  Chain / march in us, generalized minmod +
+// HLLC where not said:
+//   MHM + PPM        FP64 5 groups 25.3 / 25.8, 6 27.1 / 26.0; FP32 7 20.9 /
+//                    21.3, 8 21.7 / 21.4; dual energy FP64 11 33.2 / 34.1, 12
+//                    42.4 / 34.4; FP32 10 26.2 / 26.1, 11 26.9 / 26.0
+//   MHM + PLM, dual  one group FP64 19.6 / 16.0, FP32 15.8 / 13.1
+//   CTU + PLM        FP64 4 35.5 / 35.8, 6 39.8 / 36.2; FP32 6 30.6 / 31.1, 7
+//                    32.0 / 31.1; characteristic FP64 5 39.2 / 38.6, van Leer +
+//                    Roe 11 44.4 / 46.4, 12 49.7 / 46.8, 20 62.2 / 64.5, 24 73.1 /
+//                    66.0; FP32 7 32.1 / 32.7, 8 33.6 / 32.8 (van Leer + Roe 33.9 /
+//                    34.2)
+//     dual energy    FP64 14 56.8 / 56.9, 16 60.6 / 57.7, 18 65.1 / 72.9, 24 81.7 /
+//                    75.1; FP32 5 34.3 / 35.1, 7 37.7 / 35.2
+//   CTU + PPM        FP64 52 141 / 144, 56 153 / 145, 72 188 / 221, 80 209 / 223, 96
+//                    243 / 226; FP32 52 78.8 / 79.7, 56 83.1 / 80.6
+//     dual energy    FP64 64 203 / 204, 96 299 / 316, 112 349 / 326; FP32 52 92.7 /
+//                    94.5, 56 97.8 / 95.4, 72 119 / 134, 80 131 / 135, 96 152 / 136
+bool ext_uses_chain(int64_t G, bool fp64, const ExtOpts& o) {
+  if (!o.ctu) return o.ppm && G <= (fp64 ? (o.de ? 11 : 5) : (o.de ? 10 : 7));
+  if (o.ppm) {
+    if (fp64 && o.de) return G <= 96;
+    return G <= 52 || (G > 64 && G <= (fp64 || o.de ? 80 : 0));
+  }
+  if (!fp64) return G <= (o.chr && !o.de ? 8 : 6);
+  const bool second_round = G > 16 && G <= 20;
+  if (o.de) return G <= 14 || second_round;
+  if (o.chr && o.lim != 0) return G <= 11 || second_round;
+  return G <= 4;
 }
 
 template <typename T, int NF, bool kPpm>
@@ -432,7 +452,7 @@ template <typename T>
 hipError_t launch_ext_step(const T* U_pad, T* U_out, int64_t G, int ghost, const Gas<T>& gas, const double* dt_dev,
                            double dx, const ExtOpts& o, int* n_bad, T* work, T* face_flux, hipStream_t stream) {
   if (G == 0) return hipSuccess;
-  if (use_chain(G, o)) {
+  if (ext_uses_chain(G, sizeof(T) == 8, o)) {
     if (o.de) return chain_step<T, 6>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, nullptr, stream);
     return chain_step<T, 5>(U_pad, U_out, G, ghost, gas, dt_dev, dx, o, n_bad, work, face_flux, stream);
   }

@@ -116,6 +116,7 @@ def load():
         "hydro_set_batched_tuned": (i32, [P, i32, i32]),
         "hydro_get_batched_variant": (i32, [P, i32]),
         "hydro_padded_segments": (i32, [i64, i32]),
+        "hydro_ext_uses_chain": (i32, [i64, i32, i32, i32]),
         "hydro_level_segments": (i32, [P, i32, i32, i32, i32, i32, i32]),
         "hydro_batched_segments": (i32, [P, P, i32, i32]),
         "hydro_autotune_batched": (i32, [P, P, i32, i32, f64, P, i32, P, P]),
@@ -662,6 +663,13 @@ def padded_segments(n_groups: int, dtype) -> int:
     words (1: whole groups)."""
     return _segments(load().hydro_padded_segments(int(n_groups), F64 if dtype == torch.float64 else F32),
                      "hydro_padded_segments")
+
+
+def ext_uses_chain(n_groups: int, ghost: int, dtype, scheme: int) -> bool:
+    """Whether advance_ext runs these groups as the chain of kernels."""
+    return bool(_segments(load().hydro_ext_uses_chain(int(n_groups), int(ghost),
+                                                      F64 if dtype == torch.float64 else F32, int(scheme)),
+                          "hydro_ext_uses_chain"))
 
 
 def level_segments(ng: Sequence[int], dtype, with_cfl: bool = False, with_patch_dt: bool = False,
