@@ -47,10 +47,10 @@ __device__ __forceinline__ void store_pair(T* d, T a, T b) {
 template <typename T, bool kPair>
 __global__ __launch_bounds__(256) void fill_ghosts_kernel(const T* __restrict__ level, T* __restrict__ U_pad,
                                                           int ngx, int ngy, int ngz, int gh, unsigned int planes,
-                                                          BC6 bc) {
+                                                          bool blocked, BC6 bc) {
   const int P = 16 + 2 * gh, H = P / 2;
   const unsigned int per = (planes + 7u) / 8u;
-  const unsigned int blk = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+  const unsigned int blk = blocked ? (blockIdx.x & 7u) * per + (blockIdx.x >> 3) : blockIdx.x;
   if (blk >= planes) return;
   const int z = int(blk % unsigned(P));
   const unsigned int g = blk / unsigned(P);
@@ -142,12 +142,19 @@ hipError_t launch_fill_ghosts(const T* level, T* U_pad, int ngx, int ngy, int ng
   for (int i = 0; i < 6; ++i) b.b[i] = bc[i];
   const unsigned n = unsigned(planes / 5);  // workgroups: padded planes of all five fields
   const dim3 grid((n + 7) / 8 * 8);
+  // a contiguous range of planes per XCD, but round robin for FP64 blocks with
+  // wide ghost zones of few groups, where eight distant write streams collide (us,
+  // contiguous / round robin, and 8-byte stores per field before: 64 groups with
+  // 16 ghosts 71.9 / 48.4, 61.7, with 12 39.7 / 28.4, 39.3; 128 with 14 111 / 92, 104;
+  // but 256 with 16 281 / 309, 353; 96 with 11 53.6 / 55.4, 56.2; FP32 64 with 16
+  // 34.8 / 34.6, 57.5)
+  const bool blocked = sizeof(T) == 4 || ghost < 12 || int64_t(ngx) * ngy * ngz > 128;
   if (reinterpret_cast<uintptr_t>(U_pad) % (2 * sizeof(T)) == 0)
     hipLaunchKernelGGL((fill_ghosts_kernel<T, true>), grid, dim3(256), 0, stream, level, U_pad, ngx, ngy, ngz, ghost,
-                       n, b);
+                       n, blocked, b);
   else
     hipLaunchKernelGGL((fill_ghosts_kernel<T, false>), grid, dim3(256), 0, stream, level, U_pad, ngx, ngy, ngz, ghost,
-                       n, b);
+                       n, blocked, b);
   return hipGetLastError();
 }
 
