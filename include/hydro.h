@@ -332,11 +332,12 @@ int hydro_amr_fill_ghosts(const hydro_amr_level_t* fine, const hydro_amr_level_t
  *   (those of hydro_advance), reading the level's states (fine->U_dev, not
  *   modified) directly: hydro_amr_fill_ghosts + hydro_advance_ext without the
  *   padded copy of the level, the same results.  coarse, coarse_old_dev,
- *   coarse_new_dev, a, bc_host, ghost (2..16): as for hydro_amr_fill_ghosts;
+ *   coarse_new_dev, a, bc_host: as for hydro_amr_fill_ghosts; ghost: 2..16 (the
+ *   step reads two layers whatever it is);
  *   dt, dx, gamma, scheme, theta, n_bad_dev: as for hydro_advance.
  *   U_out_dev      [G][5][16^3] new states; must not overlap the old ones
- *   U_pad_dev      scratch [G][5][P^3]: only ghost cells that no sibling holds
- *                  are written and read
+ *   U_pad_dev      scratch [G][5][20^3 - 16^3]: of the cells two deep around a
+ *                  group those that no sibling holds are written and read
  *   finer          the next finer level, or NULL if there is none
  *   face_flux_dev  [G][9][5][16][16], layout of hydro_advance_ext: the planes
  *                  that hydro_amr_flux_accumulate and hydro_amr_fixup read are

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void amr_fill_kernel(const T* __restrict__ Uf,
 template <typename T>
 __global__ __launch_bounds__(256) void amr_fill_open_kernel(AmrLevelArgs F, const T* __restrict__ Cold,
                                                             const T* __restrict__ Cnew, LevelDev C, T a, AmrBc bc,
-                                                            int ghost, T* __restrict__ pad) {
+                                                            T* __restrict__ shell) {
   __shared__ int sib[27];
   __shared__ int open;
   const int64_t g = blockIdx.x;
@@ -137,8 +137,6 @@ __global__ __launch_bounds__(256) void amr_fill_open_kernel(AmrLevelArgs F, cons
   }
   __syncthreads();
   if (!open) return;
-  const int P = 16 + 2 * ghost;
-  const int64_t P3 = int64_t(P) * P * P;
   const int M0 = 16 * C.n[0], M1 = 16 * C.n[1], M2 = 16 * C.n[2];
   // the 488 coarse cells around the parent patch: two 10 x 10 layers, then the
   // 36 of the rim of each of the 8 layers between
@@ -184,14 +182,15 @@ __global__ __launch_bounds__(256) void amr_fill_open_kernel(AmrLevelArgs F, cons
     at(0, 0, 1, Up);
 #pragma unroll
     for (int q = 0; q < 5; ++q) s2[q] = minmod2(U0[q] - Um[q], Up[q] - U0[q]);
-    T* d = pad + g * 5 * P3 + (int64_t(2 * cz + ghost) * P + (2 * cy + ghost)) * P + (2 * cx + ghost);
+    T* d = shell + g * 5 * kShellCells;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
+      const unsigned at = shell_cell(2 * cx + (c & 1), 2 * cy + ((c >> 1) & 1), 2 * cz + (c >> 2));
       const T off0 = (c & 1) ? T(0.25) : T(-0.25), off1 = (c & 2) ? T(0.25) : T(-0.25),
               off2 = (c & 4) ? T(0.25) : T(-0.25);
 #pragma unroll
       for (int q = 0; q < 5; ++q)
-        d[q * P3 + ((c >> 2) * P + ((c >> 1) & 1)) * P + (c & 1)] = ((U0[q] + s0[q] * off0) + s1[q] * off1) + s2[q] * off2;
+        d[q * kShellCells + at] = ((U0[q] + s0[q] * off0) + s1[q] * off1) + s2[q] * off2;
     }
   }
 }
@@ -314,13 +313,13 @@ hipError_t launch_amr_fill(const T* Uf, const AmrLevelArgs& F, const T* Cold, co
 
 template <typename T>
 hipError_t launch_amr_fill_open(const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C, double a,
-                                const int bc[6], int ghost, T* pad, hipStream_t stream) {
+                                const int bc[6], T* shell, hipStream_t stream) {
   if (F.G == 0) return hipSuccess;
   if (F.G > (int64_t(1) << 31) - 1) return hipErrorInvalidValue;
   AmrBc b;
   for (int i = 0; i < 6; ++i) b.v[i] = bc[i];
   hipLaunchKernelGGL(amr_fill_open_kernel<T>, dim3(unsigned(F.G)), dim3(256), 0, stream, F, Cold, Cnew, to_dev(C),
-                     T(a), b, ghost, pad);
+                     T(a), b, shell);
   return hipGetLastError();
 }
 
@@ -354,7 +353,7 @@ hipError_t launch_amr_fixup(T* Uc, const AmrLevelArgs& C, const AmrLevelArgs& F,
   template hipError_t launch_amr_fill<T>(const T*, const AmrLevelArgs&, const T*, const T*, const AmrLevelArgs&,    \
                                          double, const int*, int, T*, hipStream_t);                                 \
   template hipError_t launch_amr_fill_open<T>(const AmrLevelArgs&, const T*, const T*, const AmrLevelArgs&, double, \
-                                              const int*, int, T*, hipStream_t);                                    \
+                                              const int*, T*, hipStream_t);                                         \
   template hipError_t launch_amr_accumulate<T>(const AmrLevelArgs&, const T*, double, const int*, T*, hipStream_t); \
   template hipError_t launch_amr_restrict<T>(const T*, const AmrLevelArgs&, T*, const AmrLevelArgs&, hipStream_t);  \
   template hipError_t launch_amr_fixup<T>(T*, const AmrLevelArgs&, const AmrLevelArgs&, const T*, const T*, double, \

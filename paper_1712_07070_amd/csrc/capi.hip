@@ -882,8 +882,8 @@ int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* co
     if (!amr_level_ok(finer, false) || !amr_pair_ok(finer, fine)) return HYDRO_EINVAL;
     N = amr_args(finer);
   }
-  const int64_t P = 16 + 2 * ghost, G = fine->n_groups;
-  const size_t es = dtype_size(dtype), ub = size_t(G) * 5 * 4096 * es, pb = size_t(G) * 5 * P * P * P * es,
+  const int64_t G = fine->n_groups;
+  const size_t es = dtype_size(dtype), ub = size_t(G) * 5 * 4096 * es, pb = size_t(G) * 5 * gh::kShellCells * es,
                fb = size_t(G) * 9 * 5 * 256 * es;
   if (overlap(U_pad_dev, pb, fine->U_dev, ub) || overlap(U_out_dev, ub, fine->U_dev, ub) ||
       overlap(U_out_dev, ub, U_pad_dev, pb) || overlap(face_flux_dev, fb, fine->U_dev, ub) ||
@@ -895,12 +895,12 @@ int hydro_amr_advance(const hydro_amr_level_t* fine, const hydro_amr_level_t* co
     using T = decltype(zero);
     if (coarse != nullptr) {  // a level without one covers the domain: no cell is missing
       const hipError_t e = gh::launch_amr_fill_open(amr_args(fine), static_cast<const T*>(coarse_old_dev),
-                                                    static_cast<const T*>(coarse_new_dev), C, a, bc_host, ghost,
+                                                    static_cast<const T*>(coarse_new_dev), C, a, bc_host,
                                                     static_cast<T*>(U_pad_dev), s);
       if (e != hipSuccess) return e;
     }
     return gh::launch_mhm_amr(static_cast<const T*>(fine->U_dev), static_cast<T*>(U_out_dev), amr_args(fine),
-                              static_cast<const T*>(U_pad_dev), ghost, bc_host, make_gas<T>(gamma, theta, dt, dx),
+                              static_cast<const T*>(U_pad_dev), bc_host, make_gas<T>(gamma, theta, dt, dx),
                               first_order, ws, n_bad_dev, static_cast<T*>(face_flux_dev), N, s);
   };
   return device_status(dtype == HYDRO_F64 ? go(0.0) : go(0.0f));

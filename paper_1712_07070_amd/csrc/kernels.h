@@ -239,15 +239,34 @@ __device__ __forceinline__ unsigned amr_outflow_faces(const AmrLevelArgs& F, con
          unsigned(bc.v[2] != 0 && p1 == 0) << 2 | unsigned(bc.v[3] != 0 && p1 == F.n[1] - 1) << 3 |
          unsigned(bc.v[4] != 0 && p2 == 0) << 4 | unsigned(bc.v[5] != 0 && p2 == F.n[2] - 1) << 5;
 }
-// Padded blocks: only the cells the default step reads where no sibling is.
+// Scratch of the direct step, [G][5][kShellCells]: the cells two deep around a
+// group (those inside are its own), of which only the ones that the step reads
+// and no sibling holds are written.  The rims of planes -2 .. 17 (rows y = -2, -1,
+// 16, 17, then x = -2, -1, 16, 17 of the others), then planes z = -2, -1, 16, 17
+// over the group.  The padded block of 22^3 (3 ghosts) took 2.7 times as much, and
+// with the second state buffer of the direct step 1.4 times what a padded step
+// holds.
+constexpr int kShellCells = 20 * 20 * 20 - 16 * 16 * 16;
+__host__ __device__ __forceinline__ bool shell_in(int x, int y) { return x >= 0 && x <= 15 && y >= 0 && y <= 15; }
+// place of a column in a plane, and offset of plane z
+__host__ __device__ __forceinline__ unsigned shell_column(int x, int y) {
+  if (shell_in(x, y)) return unsigned(y * 16 + x);
+  return unsigned(y < 0 ? (y + 2) * 20 + (x + 2) : y > 15 ? (y - 14) * 20 + (x + 2) : 80 + y * 4 + (x < 0 ? x + 2 : x - 14));
+}
+__host__ __device__ __forceinline__ unsigned shell_plane(bool in, int z) {
+  return unsigned(in ? 2880 + (z < 0 ? z + 2 : z - 14) * 256 : (z + 2) * 144);
+}
+__host__ __device__ __forceinline__ unsigned shell_cell(int x, int y, int z) {
+  return shell_column(x, y) + shell_plane(shell_in(x, y), z);
+}
 template <typename T>
 hipError_t launch_amr_fill_open(const AmrLevelArgs& F, const T* Cold, const T* Cnew, const AmrLevelArgs& C, double a,
-                                const int bc[6], int ghost, T* pad, hipStream_t stream);
-// The default step of a level from its states and those blocks (mhm_amr.hip),
+                                const int bc[6], T* shell, hipStream_t stream);
+// The default step of a level from its states and those cells (mhm_amr.hip),
 // with the face fluxes that flux registers read (N: the next finer level, its map
 // null if there is none).
 template <typename T>
-hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* pad, int ghost, const int bc[6],
+hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* shell, const int bc[6],
                           const Gas<T>& gas, int first_order, int ws, int* n_bad, T* face_flux,
                           const AmrLevelArgs& N, hipStream_t stream);
 template <typename T>

@@ -1,7 +1,7 @@
 // The MHM step of an AMR level read from its own storage (hydro_amr_advance):
 // a group's cells and its siblings' from the level's states through the
-// lattice map, the cells where no sibling is from a padded block in which
-// only those are filled (amr.hip: amr_fill_open).  The padded form wrote and
+// lattice map, the cells where no sibling is from scratch cells around the group
+// of which only those are filled (amr.hip: amr_fill_open).  The padded form wrote and
 // read back every group's 22^3 block for each substep; here only the groups
 // at a coarse-fine interface touch theirs.
 
@@ -36,7 +36,7 @@ __device__ __forceinline__ bool amr_flux_read(const AmrLevelArgs& F, const AmrLe
 
 template <typename T, class Z>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void mhm_amr_kernel(
-    const T* __restrict__ U, T* __restrict__ Uout, AmrLevelArgs F, const T* __restrict__ pad, int gh, AmrBc bc,
+    const T* __restrict__ U, T* __restrict__ Uout, AmrLevelArgs F, const T* __restrict__ shell, AmrBc bc,
     Gas<T> gas, int first_order, int ws, int* __restrict__ n_bad, T* __restrict__ face_flux, AmrLevelArgs N, int segs) {
   __shared__ Smem<T> sm;
   __shared__ int sib[27];
@@ -57,9 +57,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     if (t == 0) planes = m;
   }
   __syncthreads();
-  const int P = 16 + 2 * gh;
-  const AmrSource<T> src{U, pad + g * 5 * int64_t(P) * P * P, sib, __builtin_amdgcn_readfirstlane(sib[4]),
-                         __builtin_amdgcn_readfirstlane(sib[13]), __builtin_amdgcn_readfirstlane(sib[22]), P, gh,
+  const AmrSource<T> src{U, shell + g * 5 * kShellCells, sib, __builtin_amdgcn_readfirstlane(sib[4]),
+                         __builtin_amdgcn_readfirstlane(sib[13]), __builtin_amdgcn_readfirstlane(sib[22]),
                          amr_outflow_faces(F, bc, p0, p1, p2)};
   const unsigned ff_planes = __builtin_amdgcn_readfirstlane(planes);
   T* ff = ff_planes != 0 ? face_flux + g * 9 * 5 * 256 : nullptr;
@@ -76,7 +75,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 }  // namespace
 
 template <typename T>
-hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* pad, int ghost, const int bc[6],
+hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* shell, const int bc[6],
                           const Gas<T>& gas, int first_order, int ws, int* n_bad, T* face_flux,
                           const AmrLevelArgs& N,
                           hipStream_t stream) {
@@ -87,18 +86,18 @@ hipError_t launch_mhm_amr(const T* U, T* U_out, const AmrLevelArgs& F, const T* 
   AmrBc b;
   for (int i = 0; i < 6; ++i) b.v[i] = bc[i];
   if (segs > 1)
-    hipLaunchKernelGGL((mhm_amr_kernel<T, ZPart>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, U, U_out, F, pad,
-                       ghost, b, gas, first_order, ws, n_bad, face_flux, N, segs);
+    hipLaunchKernelGGL((mhm_amr_kernel<T, ZPart>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, U, U_out, F, shell,
+                       b, gas, first_order, ws, n_bad, face_flux, N, segs);
   else
-    hipLaunchKernelGGL((mhm_amr_kernel<T, ZAll>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, U, U_out, F, pad,
-                       ghost, b, gas, first_order, ws, n_bad, face_flux, N, 1);
+    hipLaunchKernelGGL((mhm_amr_kernel<T, ZAll>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, U, U_out, F, shell,
+                       b, gas, first_order, ws, n_bad, face_flux, N, 1);
   return hipGetLastError();
 }
 
-template hipError_t launch_mhm_amr<double>(const double*, double*, const AmrLevelArgs&, const double*, int, const int*,
+template hipError_t launch_mhm_amr<double>(const double*, double*, const AmrLevelArgs&, const double*, const int*,
                                            const Gas<double>&, int, int, int*, double*,
                                            const AmrLevelArgs&, hipStream_t);
-template hipError_t launch_mhm_amr<float>(const float*, float*, const AmrLevelArgs&, const float*, int, const int*,
+template hipError_t launch_mhm_amr<float>(const float*, float*, const AmrLevelArgs&, const float*, const int*,
                                           const Gas<float>&, int, int, int*, float*,
                                           const AmrLevelArgs&, hipStream_t);
 

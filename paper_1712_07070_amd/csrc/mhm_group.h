@@ -75,46 +75,47 @@ __device__ __forceinline__ void load_cons(const Src& src, typename Src::Off col,
 
 // A group of an AMR level: cells of the group and of the siblings around it
 // are read from the level's states, cells where no sibling is from the
-// group's padded block (interpolated there beforehand, only those).  A
+// group's scratch cells (interpolated there beforehand, only those).  A
 // column's "offset" holds its coordinates, (y + 2) * 32 + (x + 2), clamped
-// where the domain ends with outflow, as z is at the load.
+// where the domain ends with outflow, as z is at the load, and above them its
+// place in a plane of the scratch cells and whether it is one of the group's.
 template <typename T>
 struct AmrSource {
   using Off = unsigned int;
   const T* U;          // states of the level
-  const T* pad;        // this group's padded block
+  const T* shell;      // this group's scratch cells (shell_cell)
   const int* sib;      // LDS: sibling groups, [z][y][x] class (below, in, above), -1 where absent
   int below, self, above;  // sib of the centre column
-  int P, gh;
   unsigned out;        // bits x-, x+, y-, y+, z-, z+: the group touches an outflow face of the domain
   static __device__ __forceinline__ int clamp(int i, unsigned lo, unsigned hi) {
     return (i < 0 && lo) ? 0 : (i > 15 && hi) ? 15 : i;
   }
   __device__ Off col(int x, int y) const {
-    return unsigned((clamp(y, out & 4u, out & 8u) + 2) * 32 + clamp(x, out & 1u, out & 2u) + 2);
+    const int xc = clamp(x, out & 1u, out & 2u), yc = clamp(y, out & 4u, out & 8u);
+    return unsigned(shell_in(xc, yc)) << 18 | shell_column(xc, yc) << 10 | unsigned((yc + 2) * 32 + xc + 2);
   }
 };
 template <bool kI, typename T>
 __device__ __forceinline__ void load_cons(const AmrSource<T>& src, unsigned int col, int z, T U[5]) {
   const int zc = AmrSource<T>::clamp(z, src.out & 16u, src.out & 32u);
-  const int x = int(col & 31u) - 2, y = int(col >> 5) - 2, cz = (zc + 16) >> 4;
-  const unsigned P3 = unsigned(src.P) * src.P * src.P;
+  const int x = int(col & 31u) - 2, y = int((col >> 5) & 31u) - 2, cz = (zc + 16) >> 4;
   const unsigned in = unsigned((zc & 15) * 256 + (y & 15) * 16 + (x & 15));
-  const unsigned at = unsigned(((zc + src.gh) * src.P + (y + src.gh)) * src.P + (x + src.gh));
   // members read before they are selected from: a select of their addresses
   // would keep the source in memory
-  const T *Us = src.U, *pad = src.pad;
+  const T *Us = src.U, *shell = src.shell;
   if constexpr (kI) {
     const int s0 = src.below, s1 = src.self, s2 = src.above;
     const int s = cz == 0 ? s0 : cz == 1 ? s1 : s2;  // uniform
-    const T* b = s >= 0 ? Us + int64_t(s) * (5 * 4096) : pad;
-    const unsigned o = s >= 0 ? in : at, fs = s >= 0 ? 4096u : P3;
+    const T* b = s >= 0 ? Us + int64_t(s) * (5 * 4096) : shell;
+    const unsigned o = s >= 0 ? in : unsigned(y * 16 + x) + shell_plane(true, zc);
+    const unsigned fs = s >= 0 ? 4096u : unsigned(kShellCells);
 #pragma unroll
     for (int q = 0; q < 5; ++q) U[q] = b[o + q * fs];
   } else {
     const int s = src.sib[cz * 9 + ((y + 16) >> 4) * 3 + ((x + 16) >> 4)];
-    const T* b = s >= 0 ? Us + (int64_t(s) * (5 * 4096) + in) : pad + at;
-    const unsigned fs = s >= 0 ? 4096u : P3;
+    const unsigned at = ((col >> 10) & 255u) + ((col >> 18) != 0 ? shell_plane(true, zc) : shell_plane(false, zc));
+    const T* b = s >= 0 ? Us + (int64_t(s) * (5 * 4096) + in) : shell + at;
+    const unsigned fs = s >= 0 ? 4096u : unsigned(kShellCells);
 #pragma unroll
     for (int q = 0; q < 5; ++q) U[q] = b[q * fs];
   }

@@ -38,6 +38,7 @@ RIEMANN_HLLC, RIEMANN_ROE, RIEMANN_HLLE = 0 << 16, 1 << 16, 2 << 16
 DUAL_ENERGY = 1 << 18
 BATCH_WORK_WORDS = 16       # uint32 words of the batched kernel's work buffer
 BATCHED_VARIANTS = 16       # launch shapes of the batched kernel
+AMR_SHELL_CELLS = 20 ** 3 - 16 ** 3   # scratch cells per field and group of hydro_amr_advance
 
 _lib = None
 
@@ -1119,8 +1120,11 @@ class AmrSolver:
                 raise ValueError("level %d: states must be [G,5,16,16,16] of one dtype" % l)
             self.pos.append(torch.from_numpy(p).to(device))
             self.maps.append(torch.from_numpy(m).to(device))
+            # padded blocks, or the scratch cells around the groups of a direct
+            # step: with its second state buffer no more memory either way
             P = 16 + 2 * self.ghost
-            self.pad.append(torch.empty((G, 5, P, P, P), dtype=dtype, device=device))
+            self.pad.append(torch.empty((G, 5, AMR_SHELL_CELLS) if self.direct else (G, 5, P, P, P), dtype=dtype,
+                                        device=device))
             self.work.append(ext_workspace(G, self.ghost, dtype, self.scheme, device))
             self.flux.append(torch.empty((G, 9, 5, 16, 16), dtype=dtype, device=device))
             self.alt.append(torch.empty_like(self.U[l]) if self.direct or l + 1 < self.nl else None)

@@ -63,3 +63,66 @@ def test_failed_substep_leaves_the_solver_usable(lib, fail_at):
     lib.steps, lib.fail_at = [], None
     s.step(1e-3)
     assert lib.steps == clean
+
+
+@pytest.mark.parametrize("ghost", [2, 3, 5])
+@pytest.mark.parametrize("n0,boxes", [(2, ()), (3, (((2, 4),) * 3,)), (3, (((0, 6),) * 3, ((0, 12),) * 3)),
+                                      (3, (((2, 4),) * 3, ((5, 7),) * 3))])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_direct_steps_take_no_more_memory_than_padded_ones(lib, dtype, n0, boxes, ghost):
+    """The second state buffers of the direct step fit in what its scratch cells
+    take less than padded blocks (which the other words hold, with old states
+    for all levels but the finest): the largest hierarchy that fits the card is
+    no smaller."""
+    def held(s):
+        return sum(t.numel() * t.element_size() for ts in (s.pad, s.work, s.flux, s.alt, s.reg) for t in ts
+                   if t is not None)
+    direct = solver(dtype=dtype, n0=n0, boxes=boxes, ghost=ghost)
+    padded = solver(hydro.SCHEME_MHM_PLM_HLLC | hydro.RIEMANN_ROE, dtype=dtype, n0=n0, boxes=boxes, ghost=ghost)
+    assert direct.direct and not padded.direct
+    assert held(direct) <= held(padded)
+
+
+# The scratch cells are addressed by arithmetic that runs only on the device; an
+# index used twice or beyond the block would give wrong cells (or write outside
+# the buffer).  The function is taken from the kernel header as written and
+# compiled for the host.
+_SHELL_CHECK = r"""
+#include <cstdio>
+#include <vector>
+%s
+int main() {
+  std::vector<int> seen(kShellCells, 0);
+  int cells = 0, bad = 0;
+  for (int z = -2; z <= 17; ++z) for (int y = -2; y <= 17; ++y) for (int x = -2; x <= 17; ++x) {
+    if (x >= 0 && x <= 15 && y >= 0 && y <= 15 && z >= 0 && z <= 15) continue;
+    const unsigned i = shell_cell(x, y, z);
+    ++cells;
+    if (i >= unsigned(kShellCells)) ++bad;
+    else ++seen[i];
+  }
+  for (int v : seen) bad += v != 1;
+  printf("%%d %%d\n", cells, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_scratch_cells_of_a_group_are_distinct(tmp_path):
+    import os
+    import re
+    import shutil
+    import subprocess
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = open(os.path.join(root, "paper_1712_07070_amd", "csrc", "kernels.h")).read()
+    i = src.index("constexpr int kShellCells")
+    j = src.index("}\n", src.index(" shell_cell(", i)) + 2
+    body = re.sub(r"__host__ __device__ __forceinline__|__device__ __forceinline__", "inline", src[i:j])
+    cpp, exe = tmp_path / "shell.cpp", tmp_path / "shell"
+    cpp.write_text(_SHELL_CHECK % body)
+    subprocess.run([gxx, "-O2", "-std=c++17", str(cpp), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.stdout.split() == [str(20 ** 3 - 16 ** 3), "0"]
