@@ -503,9 +503,11 @@ int set_batched(hydro_ctx* ctx, int32_t dtype, int32_t variant, bool by_caller) 
   std::lock_guard<std::mutex> lk(ctx->mu);
   ctx->batched_sel[dtype] = variant;
   ctx->batched_explicit[dtype] = by_caller;
-  const std::string prefix = std::string("batched/") + dtype_name(dtype) + "/";
-  for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
-    it = it->first.compare(0, prefix.size(), prefix) == 0 ? ctx->tuned.erase(it) : std::next(it);
+  for (const char* form : {"batched/", "batched-cfl/"}) {
+    const std::string prefix = std::string(form) + dtype_name(dtype) + "/";
+    for (auto it = ctx->tuned.begin(); it != ctx->tuned.end();)
+      it = it->first.compare(0, prefix.size(), prefix) == 0 ? ctx->tuned.erase(it) : std::next(it);
+  }
   return HYDRO_OK;
 }
 

@@ -107,3 +107,18 @@ def test_batched_tuner_lifts_a_shape_set_before(tmp_path):
     hydro.autotune_batched(lv, 1.4, work, reps=1, ctx=ctx)
     assert ctx.num_tuned() == 1 and hydro.batched_segments(lv, ctx) > 1
     assert hydro.batched_segments(lv[:1], ctx) == 1   # other levels: still as set
+
+
+def test_batched_shape_set_by_the_caller_replaces_tuned_ones_of_both_forms(host, tmp_path):
+    """hydro_set_batched_variant stands in place of the tuned entries of its dtype,
+    also those of launches that reduce CFL time-steps."""
+    path = tmp_path / "tune.json"
+    path.write_text('{"version": 1, "entries": {"batched/f64/2x2x2": 3, "batched-cfl/f64/2x2x2": 4, '
+                    '"batched-cfl/f32/2x2x2": 2}}')
+    ctx = hydro.Context(str(path))
+    dt = torch.zeros(1, dtype=torch.float64)
+    cfl = entries([(2, 2, 2)], torch.float64, dict(c_cfl=0.5, dt_next=dt))
+    assert ctx.num_tuned() == 3 and hydro.batched_segments(cfl, ctx) > 1
+    hydro.set_batched_variant(torch.float64, 5, ctx=ctx)
+    assert ctx.num_tuned() == 1
+    assert hydro.batched_segments(cfl, ctx) == hydro.batched_segments(entries([(2, 2, 2)], torch.float64), ctx) == 1
