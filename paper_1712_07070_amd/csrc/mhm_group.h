@@ -147,12 +147,12 @@ struct Smem {
 //   DefaultScheme  generalized minmod on primitive variables and HLLC (the
 //                  limiter specialized in its own inlined copy, see
 //                  process_group), with the optional branch record;
-//   ExtScheme      any MHM + PLM word of the other options (run-time
-//                  ExtOpts: generalized minmod, van Leer, van Albada or
-//                  hybrid limiter, on primitive or characteristic variables;
-//                  HLLC, Roe or HLLE; either wave-speed option; first order):
-//                  the same half step with the slopes of ext_slopes and the
-//                  fluxes of riemann_any.
+//   ExtSchemeT     any MHM + PLM word of the other options (ExtOpts:
+//                  generalized minmod, van Leer, van Albada or hybrid limiter,
+//                  on primitive or characteristic variables; HLLC, Roe or
+//                  HLLE; either wave-speed option; first order): the same
+//                  half step with the slopes of ext_slopes and the fluxes of
+//                  riemann_any.
 struct DefaultScheme {};
 // kChr (0 / 1) fixes the characteristic projection at compile time, kRoe
 // the solver family (1: Roe, 0: HLLC or HLLE) and kLim the limiter of a
@@ -175,7 +175,6 @@ struct ExtSchemeT {
     return r;
   }
 };
-using ExtScheme = ExtSchemeT<>;
 
 template <typename T>
 __device__ __forceinline__ void scheme_half_step(const DefaultScheme&, const T Wc[5], const T Wn[3][2][5],

@@ -12,13 +12,13 @@ namespace gh {
 
 namespace {
 
-// The low occupancy target in FP32 and the high one in FP64: two waves per
-// SIMD in both, as for the whole-group kernels.
-template <typename T>
+// Waves per SIMD asked for: the low occupancy target in FP32 and the high one in
+// FP64, as for the whole-group kernels.  FP64 gets two, FP32 three (144-165
+// VGPRs), which plm_segments counts with.
 constexpr int kSegWaves = 2;
 
 template <typename T, bool kCfl>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_level_seg_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves))) void mhm_level_seg_kernel(
     const T* __restrict__ level, T* __restrict__ level_out, LevelGeom geo, Gas<T> gas,
     const double* __restrict__ dt_dev, double dx, int first_order, int ws, int* __restrict__ n_bad, CflOut cfl,
     int segs) {
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
 // The groups of every level of a batched launch, one workgroup per segment
 // (no queue: a launch this small has one round of workgroups).
 template <typename T, bool kCfl>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_batched_seg_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves))) void mhm_batched_seg_kernel(
     BatchArgs<T> args, Gas<T> gas, int first_order, int ws, int* __restrict__ n_bad, int segs) {
   __shared__ Smem<T> sm;
   __shared__ double cfl_slots[kCfl ? 2 * kCflHalfStride : 1];
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWa
 }
 
 template <typename T, bool kFlux>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves<T>))) void mhm_padded_seg_kernel(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kSegWaves))) void mhm_padded_seg_kernel(
     const T* __restrict__ Upad, T* __restrict__ Uout, int gh, Gas<T> gas, const double* __restrict__ dt_dev, double dx,
     int first_order, int ws, int* __restrict__ n_bad, T* __restrict__ face_flux, int segs) {
   __shared__ Smem<T> sm;
