@@ -171,7 +171,11 @@ __device__ __forceinline__ void hancock_states_vjp_stream(const T Wc[5], const G
 // limiter are the adjoint's arithmetic: with a branch per region and per side
 // the lanes of a wave took the paths in turn (192^3 FP32 level adjoint 1.23
 // ms, 1.11 with none; 128^3 FP64 607 -> 565 us); taking an x and a y face
-// in turn statement by statement gave nothing more.
+// in turn statement by statement gave nothing more.  Where all lanes took one
+// path the branches were the faster form: 512 groups FP64, noise and turbulence
+// 677 -> 631 us, a shear layer 621 -> 630, a uniform or supersonic state 604 ->
+// 630.  Tests of the whole wave around the star region and around the limiter
+// bring those two to 588 and 611, but noise to 644 and the shear layer to 642.
 template <int D, typename T>
 __device__ __forceinline__ void hllc_flux_vjp(const T Lx[5], const T Rx[5], const Gas<T>& g, int ws, const T gFx[5],
                                               T gLx[5], T gRx[5]) {
